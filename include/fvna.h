@@ -106,7 +106,8 @@ typedef struct {
     int32_t fixed_dt;          /* 1: never change dt and never reject (nu still recorded) */
     double store_scale[3];     /* FP16/BF16 storage: per-field scale of (R, M, N), in the
                                   dimensionless units above; 0 = 1.0 */
-    int32_t tile_rows;         /* rows per wavefront segment; 0 = library default */
+    int32_t tile_rows;         /* rows per wavefront segment; 0 = library default (on small
+                                  grids, tiles of a whole block instead of segments) */
 } fvna_params;
 
 /* Focused boundary source of eq. hifuBC on side x-: for the ghost rows whose
@@ -337,7 +338,8 @@ fvna_status fvna_time_step_kernel(fvna_ctx* c, int32_t reps, double* ms_per_laun
  * bitwise independent of the choice. */
 fvna_status fvna_autotune(fvna_ctx* c, int32_t* tile_rows);
 
-/* Rows per segment currently used by the step kernel. */
+/* Rows per segment (or per block tile, on small grids) currently used by the
+ * step kernel. */
 fvna_status fvna_get_tile_rows(fvna_ctx* c, int32_t* tile_rows);
 
 /* Thread-local message of the last failing call (never NULL). */

@@ -150,6 +150,16 @@ __device__ __forceinline__ void cfl_slot(Clock* c, int k, unsigned long long*& s
     else { CflSlot& q = clock_aux(c)->slot[k - 1]; sb = &q.smax_bits; fl = &q.flags; }
 }
 
+// A value every lane of the wavefront holds alike, in scalar registers.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ long long uniform(long long x)
+{
+    const unsigned lo = (unsigned)uniform((int)(x & 0xffffffffll)), hi = (unsigned)uniform((int)(x >> 32));
+    return (long long)(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double uniform(double x) { return __longlong_as_double(uniform(__double_as_longlong(x))); }
+__device__ __forceinline__ float uniform(float x) { return __int_as_float(uniform(__float_as_int(x))); }
+
 // What one attempt runs with: the time, step, buffer and domain offset of
 // its clock state, and where its largest wave speed and flags go.
 struct Attempt {
@@ -161,7 +171,7 @@ struct Attempt {
 };
 __device__ __forceinline__ Attempt attempt_of(const Clock& h, unsigned long long* sb, unsigned int* fl)
 {
-    return Attempt{h.t, h.dt, h.x_off, h.cur, sb, fl};
+    return Attempt{uniform(h.t), uniform(h.dt), uniform(h.x_off), uniform(h.cur), sb, fl};
 }
 
 // Everything a wavefront needs to know about its simulation.
@@ -182,6 +192,7 @@ struct SimDesc {
     int sr_env;                  // 0: sin^2 ramp in t; 1: packet exp(-(f tau / sr_W)^10)
     double sr_W;                 // packet half-width in periods
     double sr_t2;                // start of the second stage (+inf: none)
+    int block_rows;              // > 0: block tiles of this many rows (block_tile); 0: march_tile
     const void* rinv;            // axisymmetric: 1/(j + 1/2) for rows j = -RINV_PAD .. ny + RINV_PAD - 1,
                                  // in the arithmetic type (rinv_at)
 };
@@ -587,9 +598,73 @@ __device__ __forceinline__ void geometric_half_step(Cell<T>& q, T hr)
     q.N = fma_(-hr, v * v, q.N);
 }
 
+// x1 sweep of one row, lane-parallel: lane l holds the cell of column l, and
+// every interface is solved once (by the lane on its right).  COUNT: whether
+// its interfaces enter the CFL bookkeeping; GEO: the axisymmetric half step
+// closes the sweep (hr = dt / (2 r)).  The outermost two lanes of each end
+// come out without meaning.
+template <typename T, bool GEO, bool COUNT>
+__device__ __forceinline__ Cell<T> x1_sweep(const Cell<T>& q, T dt, T beta, T hr, Cfl<T>& acc)
+{
+    const T RL = from_lo(q.R);
+    const T Sr = RL + q.R;
+    T irho, h;
+    rcp_pair(T(1) + q.R, T(2) + Sr, irho, h);
+    const T u = q.M * irho, v = q.N * irho;
+    const T ML = from_lo(q.M), NL = from_lo(q.N);
+    const T uL = from_lo(u), vL = from_lo(v);
+    Wave<T> w;
+    T D;
+    const T spd = roe_sh(RL, ML, NL, uL, vL, q.R, q.M, q.N, u, v, beta, Sr, h, w, D);
+    if constexpr (COUNT) acc.add(spd, D);
+    // waves of the interface to the right -> products with it; the lane
+    // to the left supplies the products with the interface below
+    Wave<T> wr;
+    wr.a1 = from_hi(w.a1); wr.s1 = from_hi(w.s1); wr.r1 = from_hi(w.r1);
+    wr.a2 = from_hi(w.a2); wr.s2 = from_hi(w.s2); wr.r2 = from_hi(w.r2);
+    wr.a3 = from_hi(w.a3);
+    T tup[3], dhi[3], dlo[3];
+    wave_cross(w, wr, tup, dhi);
+    dlo[0] = from_lo(tup[0]); dlo[1] = from_lo(tup[1]); dlo[2] = from_lo(tup[2]);
+    T Gm[3], Gp[3];
+    hr_split(w, dlo, dhi, dt, Gm, Gp);
+    const T g0 = from_hi(Gm[0]), g1 = from_hi(Gm[1]), g2 = from_hi(Gm[2]);
+    Cell<T> o;
+    o.R = fma_(-dt, g0 + Gp[0], q.R);
+    o.M = fma_(-dt, g1 + Gp[1], q.M);
+    o.N = fma_(-dt, g2 + Gp[2], q.N);
+    if constexpr (GEO) geometric_half_step(o, hr);
+    return o;
+}
+
 // ---------------------------------------------------------------------------
 // Analytic boundary data (always evaluated in FP64).
+//
+// The transcendental functions and the divisions are calls, and what they
+// need of the lane and the clock is formed beside them (opaque keeps the
+// compiler from forming it ahead of the row loop).  Inlined, FP64 tanh, sine
+// and exponential made up half of a step kernel's code (205 of 116 KB for FP64
+// with them out), their constants pushed registers of the row loop to scratch,
+// and the profiles of a tile's ghost rows, which do not change from row to
+// row, were evaluated ahead of the loop by every wavefront whatever the side
+// kinds (2600 cycles of each SIMD per wavefront).
 // ---------------------------------------------------------------------------
+#define FVNA_COLD __device__ __attribute__((noinline))
+FVNA_COLD double cold_tanh(double a, double w) { return tanh(a / w); }
+FVNA_COLD double cold_sin(double x) { return sin(x); }
+FVNA_COLD double cold_div(double a, double b) { return a / b; }
+// exp(-(a / w)^10)
+FVNA_COLD double cold_packet(double a, double w)
+{
+    const double x = a / w;
+    const double x2 = x * x, x4 = x2 * x2, x8 = x4 * x4;
+    return exp(-(x8 * x2));
+}
+__device__ __forceinline__ int opaque(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
 
 // Taylor shock-like profile, eq. OurTaylorS with the rotation of Sec. 4.1,
 // at domain coordinates (x, y).  The profile is anchored on the path of a
@@ -603,7 +678,7 @@ __device__ __forceinline__ void taylor_at(const SimDesc& d, double x0, double x,
                                           double& R, double& M, double& N)
 {
     const double xi = (x - x0) * d.ta_cos + (y - d.ta_y0) * d.ta_sin;
-    R = -d.ta_amp * tanh((xi - t) / d.ta_w);
+    R = -d.ta_amp * cold_tanh(xi - t, d.ta_w);
     M = R * d.ta_cos;
     N = R * d.ta_sin;
 }
@@ -627,7 +702,7 @@ __device__ __forceinline__ SourceClock source_clock(const SimDesc& d, double t)
     if (t <= 0.0) {
         c.env = 0.0;
     } else if (t < d.sr_ramp / f) {
-        const double s = sin(M_PI * f * t / (2.0 * d.sr_ramp));
+        const double s = cold_sin(M_PI * f * t / (2.0 * d.sr_ramp));
         c.env = s * s;
     } else {
         c.env = 1.0;
@@ -642,21 +717,13 @@ template <typename T>
 __device__ __forceinline__ void source_at(const SimDesc& d, int j, const SourceClock& sc, T& R, T& M, T& N)
 {
     if (!d.src_tab) { R = M = N = T(0); return; }
-    // read-only during a step and indexed by a wave-uniform row: through the
-    // constant address space these are scalar loads, which do not wait behind
-    // the row loads in flight
-    typedef const __attribute__((address_space(4))) double* ConstRow;
-    const ConstRow e = (ConstRow)(d.src_tab + 4 * (size_t)j);
+    const double* e = d.src_tab + 4 * (size_t)j;
     double ph = sc.ft_frac + e[0];
     ph -= floor(ph);
     double env = sc.env;
-    if (d.sr_env == 1) {
-        const double x = (sc.ft + e[3]) / d.sr_W;
-        const double x2 = x * x, x4 = x2 * x2, x8 = x4 * x4;
-        env = exp(-(x8 * x2));
-    }
+    if (d.sr_env == 1) env = cold_packet(sc.ft + e[3], d.sr_W);
     T g;
-    if constexpr (sizeof(T) == 8) g = (T)(d.sr_amp * env * sin(2.0 * M_PI * ph));
+    if constexpr (sizeof(T) == 8) g = (T)(d.sr_amp * env * cold_sin(2.0 * M_PI * ph));
     else g = (T)(d.sr_amp * env) * __sinf((float)(2.0 * M_PI * ph));
     R = g;
     M = g * (T)e[1];
@@ -740,6 +807,215 @@ __device__ __forceinline__ void seg_bounds(const SimDesc& d, int seg, int& r0, i
     }
 }
 
+// Where a lane's Q^n comes from along x1: the stored column scol, the sign of
+// its normal momentum, and analytic data instead (xkind 1: Taylor, 2: focused
+// source); real_col: the lane's column is a grid column; ghost_lo / ghost_hi:
+// the left / right neighbour of this output cell is a ghost.
+template <typename T> struct XSide {
+    int scol, xkind;
+    T msign;
+    bool real_col, ghost_lo, ghost_hi;
+};
+
+template <typename T, bool EDGE>
+__device__ __forceinline__ XSide<T> x_side(const SimDesc& d, int col)
+{
+    const int nx = d.nx;
+    const bool perx = d.bc[0] == BC_PERIODIC;
+    XSide<T> x{col, 0, T(1), false, false, false};
+    if (perx) {
+        // a strip reaches at most 61 columns past the grid
+        if (nx >= WAVE) x.scol = col < 0 ? col + nx : col >= nx ? col - nx : col;
+        else x.scol = ((col % nx) + nx) % nx;
+    } else if (EDGE) {
+        if (col < 0) {
+            const int g = -col;
+            switch (d.bc[0]) {
+            case BC_REFLECT: x.scol = g - 1; x.msign = T(-1); break;
+            case BC_TAYLOR: x.xkind = 1; x.scol = 0; break;
+            case BC_SOURCE: x.xkind = 2; x.scol = 0; break;
+            default: x.scol = 0; break;
+            }
+        } else if (col >= nx) {
+            const int g = col - nx + 1;
+            switch (d.bc[1]) {
+            case BC_REFLECT: x.scol = nx - g; x.msign = T(-1); break;
+            case BC_TAYLOR: x.xkind = 1; x.scol = nx - 1; break;
+            default: x.scol = nx - 1; break;
+            }
+        }
+        x.scol = min(max(x.scol, 0), nx - 1);
+    }
+    x.real_col = perx || (col >= 0 && col < nx);
+    x.ghost_lo = EDGE && !perx && col == 0;
+    x.ghost_hi = EDGE && !perx && col == nx - 1;
+    return x;
+}
+
+// Analytic (Taylor) velocities of a ghost cell.
+template <typename T>
+__device__ __forceinline__ void taylor_uv(const SimDesc& d, long long x_off, double tn, double x, double y, T& uu,
+                                          T& vv)
+{
+    double R, M, N;
+    taylor_at(d, taylor_x0(d, x_off), x, y, tn, R, M, N);
+    uu = (T)cold_div(M, 1.0 + R);
+    vv = (T)cold_div(N, 1.0 + R);
+}
+
+// Analytic data of the ghost columns beside the grid, for many rows at once.
+// A row of an edge strip needs its focused source, or the Taylor profile at
+// two ghost columns, twice: for the x1 sweep and, three rows later, the
+// velocities for the source.  Evaluated row by row, in the few ghost lanes,
+// that put two or three FP64 tanh or sines on every row of the edge tiles,
+// which then ended the step.
+// Instead the lanes of the wavefront evaluate a group of (row, ghost column)
+// pairs together: lane = slot * per + which, with `per` = 4 lanes per row slot
+// when a side holds Taylor data (which 0, 1: columns -1, -2; 2, 3: columns nx,
+// nx + 1; the third halo column is never used) and 1 when only the source
+// acts (one value per row); a row then reads its slot with lane reads.
+// us per step, evaluated row by row / in groups: Taylor sides 4330 x 2000 FP64
+// 175 / 150, focused source 8192 x 2048 axisymmetric FP32 185 / 164, 7148 x 501
+// FP64 85 / 77.
+template <typename T> struct SideTable {
+    T R, M, N, u, v;            // cell and velocities of this lane's pair
+    int per;                    // lanes per slot; 0: no side of this strip is analytic
+    __device__ __forceinline__ int slots() const { return per == 4 ? WAVE / 4 : WAVE; }
+    __device__ __forceinline__ int slot_of(int lane) const { return per == 4 ? lane >> 2 : lane; }
+};
+
+// rmin: the tile's lowest row (no focused source above its aperture).
+template <typename T, bool EDGE>
+__device__ __forceinline__ SideTable<T> side_table(const SimDesc& d, const SourceClock& sc, int strip, int rmin)
+{
+    SideTable<T> s{T(0), T(0), T(0), T(0), T(0), 0};
+    if (EDGE && d.bc[0] != BC_PERIODIC) {
+        const int c0 = strip * OUTW;
+        const bool lo = c0 - HALO < 0, hi = c0 + OUTW + HALO - 1 > d.nx - 1;
+        if ((lo && d.bc[0] == BC_TAYLOR) || (hi && d.bc[1] == BC_TAYLOR)) s.per = 4;
+        else if (lo && d.bc[0] == BC_SOURCE && rmin + 0.5 <= sc.ap) s.per = 1;
+    }
+    return s;
+}
+
+// row: the row of this lane's slot (any row; the source's are the grid's).
+template <typename T>
+__device__ __forceinline__ void side_fill(const SimDesc& d, const SourceClock& sc, long long x_off, double tn, int row,
+                                          SideTable<T>& s)
+{
+    const int which = s.per == 4 ? (threadIdx.x & 3) : 0;
+    const int kind = which < 2 ? d.bc[0] : d.bc[1];
+    if (kind == BC_TAYLOR) {
+        const int gc = which < 2 ? -1 - which : d.nx + which - 2;
+        double R, M, N;
+        taylor_at(d, taylor_x0(d, x_off), opaque(gc) + 0.5, row + 0.5, tn, R, M, N);
+        s.R = (T)R; s.M = (T)M; s.N = (T)N;
+        s.u = (T)cold_div(M, 1.0 + R);
+        s.v = (T)cold_div(N, 1.0 + R);
+    } else if (kind == BC_SOURCE) {
+        source_at<T>(d, min(max(opaque(row), 0), d.ny - 1), sc, s.R, s.M, s.N);
+        const T ir = rcp(T(1) + s.R);
+        s.u = s.M * ir;
+        s.v = s.N * ir;
+    }
+}
+
+__device__ __forceinline__ float lane_read(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_read(double v, int l)
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(b & 0xffffffffll), l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// The analytic x side data on the loaded Q^n of a row: slot of the row's data;
+// source: whether the focused source acts on it.
+template <typename T>
+__device__ __forceinline__ void side_cell(const SimDesc& d, const XSide<T>& x, const SideTable<T>& s, int slot, int col,
+                                          bool source, Cell<T>& q)
+{
+    const int l = uniform(s.per == 4 ? 4 * slot : slot);
+    auto put = [&](int which, bool here) {
+        const T R = lane_read(s.R, l + which), M = lane_read(s.M, l + which), N = lane_read(s.N, l + which);
+        q.R = here ? R : q.R;
+        q.M = here ? M : q.M;
+        q.N = here ? N : q.N;
+    };
+    if (d.bc[0] == BC_TAYLOR) {
+        put(0, x.xkind == 1 && col == -1);
+        put(1, x.xkind == 1 && col < -1);
+    } else if (d.bc[0] == BC_SOURCE && source) {
+        put(0, x.xkind == 2);
+    }
+    if (d.bc[1] == BC_TAYLOR) {
+        put(2, x.xkind == 1 && col == d.nx);
+        put(3, x.xkind == 1 && col > d.nx);
+    }
+}
+
+// Velocities of the ghost cells beside a row's first and last column, as the
+// source step meets them (us, vs: the row's own x2-swept velocities).
+template <typename T>
+__device__ __forceinline__ void x_ghost_uv(const SimDesc& d, const XSide<T>& x, const SideTable<T>& s, int slot,
+                                           bool source, T us, T vs, T& uxl, T& vxl, T& uxr, T& vxr)
+{
+    const int b0 = d.bc[0], b1 = d.bc[1];
+    T ul = b0 == BC_REFLECT ? -us : us, ur = b1 == BC_REFLECT ? -us : us, vl = vs, vr = vs;
+    if (s.per != 0) {
+        const int l = uniform(s.per == 4 ? 4 * slot : slot);
+        if (b0 == BC_TAYLOR || (b0 == BC_SOURCE && source)) { ul = lane_read(s.u, l); vl = lane_read(s.v, l); }
+        if (b1 == BC_TAYLOR) { ur = lane_read(s.u, l + 2); vr = lane_read(s.v, l + 2); }
+    }
+    uxl = x.ghost_lo ? ul : uxl;
+    vxl = x.ghost_lo ? vl : vxl;
+    uxr = x.ghost_hi ? ur : uxr;
+    vxr = x.ghost_hi ? vr : vxr;
+}
+
+// Velocities of the rows below row 0 and above row ny - 1 (sides that are not
+// periodic), as the source meets them.
+template <typename T>
+__device__ __forceinline__ void y_ghost_uv(const SimDesc& d, long long x_off, double tn, int col, int j, T us, T vs,
+                                           T& ubl, T& vbl, T& uab, T& vab)
+{
+    if (j == 0) {
+        const int b = d.bc[2];
+        if (b == BC_REFLECT) { ubl = us; vbl = -vs; }
+        else if (b == BC_TAYLOR) taylor_uv(d, x_off, tn, opaque(col) + 0.5, -0.5, ubl, vbl);
+        else { ubl = us; vbl = vs; }
+    }
+    if (j == d.ny - 1) {
+        const int b = d.bc[3];
+        if (b == BC_REFLECT) { uab = us; vab = -vs; }
+        else if (b == BC_TAYLOR) taylor_uv(d, x_off, tn, opaque(col) + 0.5, d.ny + 0.5, uab, vab);
+        else { uab = us; vab = vs; }
+    }
+}
+
+// Source of one x2-swept row (eq. fs:source): (us, vs) its velocities, those
+// beside, below and above it; returns the new momenta.
+template <typename T, int AXI>
+__device__ __forceinline__ void source_row(const SimDesc& d, int j, T k, const Cell<T>& qs, T us, T vs,
+                                           T uxl, T vxl, T uxr, T vxr, T ubl, T vbl, T uab, T vab, T& oM, T& oN)
+{
+    const T lapu = fma_(T(-4), us, (uxl + uxr) + (ubl + uab));
+    const T lapv = fma_(T(-4), vs, (vxl + vxr) + (vbl + vab));
+    if constexpr (AXI) {
+        // cylindrical vector Laplacian: + (1/r) d/dr of each velocity, - v/r^2
+        const T ir = rinv_at<T>(d, j);
+        const T dur = T(0.5) * (uab - ubl), dvr = T(0.5) * (vab - vbl);
+        oM = fma_(k, fma_(dur, ir, lapu), qs.M);
+        oN = fma_(k, fma_(-vs, ir * ir, fma_(dvr, ir, lapv)), qs.N);
+    } else {
+        oM = fma_(k, lapu, qs.M);
+        oN = fma_(k, lapv, qs.N);
+    }
+}
+
 // State one lane carries from one x2 row to the next.  Every entry is
 // consumed by the very next row, so two copies alternated by a two-row
 // unrolled loop need no register moves.
@@ -812,7 +1088,6 @@ __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, cons
     int r0, r1;
     seg_bounds(d, seg, r0, r1);
     const double tn = at.t;
-    const double tx0 = taylor_x0(d, at.x_off);
     const T dt = (T)at.dt;
     const int cur = at.cur;
     const long long plane = d.plane;
@@ -833,36 +1108,18 @@ __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, cons
     SourceClock src_clk = {0.0, 0.0, 0.0, -1.0}; // focused source at this step's time
     if (EDGE && d.bc[0] == BC_SOURCE) src_clk = source_clock(d, tn);
 
-    // ---- where this lane's Q^n comes from (x boundary rule) ----
-    const bool incol = col >= 0 && col < nx;
-    int scol = col;
-    T msign = T(1);
-    int xkind = 0;          // 0: load; 1: Taylor; 2: focused source (else extrapolate)
-    if (perx) {
-        scol = ((col % nx) + nx) % nx;
-    } else if (EDGE) {
-        if (col < 0) {
-            const int g = -col;
-            switch (d.bc[0]) {
-            case BC_REFLECT: scol = g - 1; msign = T(-1); break;
-            case BC_TAYLOR: xkind = 1; scol = 0; break;
-            case BC_SOURCE: xkind = 2; scol = 0; break;
-            default: scol = 0; break;
-            }
-        } else if (col >= nx) {
-            const int g = col - nx + 1;
-            switch (d.bc[1]) {
-            case BC_REFLECT: scol = nx - g; msign = T(-1); break;
-            case BC_TAYLOR: xkind = 1; scol = nx - 1; break;
-            default: scol = nx - 1; break;
-            }
-        }
-        scol = min(max(scol, 0), nx - 1);
-    }
-    const bool real_col = perx || incol;
+    const XSide<T> xs = x_side<T, EDGE>(d, col);
     const bool out_lane = lane >= HALO && lane < WAVE - HALO && col < nx;
-    const bool ghost_lo = EDGE && !perx && col == 0;        // left neighbour of this output cell is a ghost
-    const bool ghost_hi = EDGE && !perx && col == nx - 1;   // right neighbour is a ghost
+    // analytic side data of rows tab0 .. tab0 + slots - 1
+    SideTable<T> tab = side_table<T, EDGE>(d, src_clk, strip, pery ? 0 : max(r0 - HALO, 0));
+    int tab0 = INT32_MIN / 2;
+    auto side_slot = [&](int r) -> int {
+        if (r < tab0 || r >= tab0 + tab.slots()) {
+            tab0 = r - HALO;               // row r is followed by the source of row r - 3
+            side_fill(d, src_clk, at.x_off, tn, tab0 + tab.slot_of(lane), tab);
+        }
+        return r - tab0;
+    };
 
     // Per-lane CFL bookkeeping, x1 and x2 interfaces apart; which lanes hold
     // real interfaces is applied once at the end (maxima and minima are
@@ -879,7 +1136,7 @@ __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, cons
                iN = make_rsrc(inN + rso, tile_bytes);
     const Rsrc oR = make_rsrc(outR + rso, tile_bytes), oM = make_rsrc(outM + rso, tile_bytes),
                oN = make_rsrc(outN + rso, tile_bytes);
-    const int vld = scol * (int)sizeof(S);
+    const int vld = xs.scol * (int)sizeof(S);
     const int vst = out_lane ? col * (int)sizeof(S) : OFF_NONE;
 
     // ---- raw loads of one row of Q^n (real row index) ----
@@ -890,7 +1147,7 @@ __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, cons
             bld(iM, vld, so, b);
             bld(iN, vld, so, c);
         } else {
-            const size_t o = (size_t)vr * pitch + (size_t)scol;
+            const size_t o = (size_t)vr * pitch + (size_t)xs.scol;
             a = inR[o];
             b = inM[o];
             c = inN[o];
@@ -904,45 +1161,12 @@ __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, cons
     auto xsweep_core = [&](auto ghost, int vr, Cell<T> q) -> Cell<T> {
         constexpr bool GHOST = decltype(ghost)::value;
         if (EDGE) {
-            q.M *= msign;
-            if (xkind == 1) {
-                double R, M, N;
-                taylor_at(d, tx0, col + 0.5, vr + 0.5, tn, R, M, N);
-                q.R = (T)R; q.M = (T)M; q.N = (T)N;
-            } else if (xkind == 2) {
-                const bool row_ok = !GHOST || (unsigned)vr < (unsigned)ny;
-                if (row_ok && vr + 0.5 <= src_clk.ap) source_at<T>(d, vr, src_clk, q.R, q.M, q.N);
-            }
+            q.M *= xs.msign;
+            if (tab.per != 0)
+                side_cell(d, xs, tab, side_slot(vr), col,
+                          (!GHOST || (unsigned)vr < (unsigned)ny) && vr + 0.5 <= src_clk.ap, q);
         }
-        const T RL = from_lo(q.R);
-        const T Sr = RL + q.R;
-        T irho, h;
-        rcp_pair(T(1) + q.R, T(2) + Sr, irho, h);
-        const T u = q.M * irho, v = q.N * irho;
-        const T ML = from_lo(q.M), NL = from_lo(q.N);
-        const T uL = from_lo(u), vL = from_lo(v);
-        Wave<T> w;
-        T D;
-        const T spd = roe_sh(RL, ML, NL, uL, vL, q.R, q.M, q.N, u, v, beta, Sr, h, w, D);
-        if constexpr (!GHOST) xacc.add(spd, D);
-        // waves of the interface to the right -> products with it; the lane
-        // to the left supplies the products with the interface below
-        Wave<T> wr;
-        wr.a1 = from_hi(w.a1); wr.s1 = from_hi(w.s1); wr.r1 = from_hi(w.r1);
-        wr.a2 = from_hi(w.a2); wr.s2 = from_hi(w.s2); wr.r2 = from_hi(w.r2);
-        wr.a3 = from_hi(w.a3);
-        T tup[3], dhi[3], dlo[3];
-        wave_cross(w, wr, tup, dhi);
-        dlo[0] = from_lo(tup[0]); dlo[1] = from_lo(tup[1]); dlo[2] = from_lo(tup[2]);
-        T Gm[3], Gp[3];
-        hr_split(w, dlo, dhi, dt, Gm, Gp);
-        const T g0 = from_hi(Gm[0]), g1 = from_hi(Gm[1]), g2 = from_hi(Gm[2]);
-        Cell<T> o2;
-        o2.R = fma_(-dt, g0 + Gp[0], q.R);
-        o2.M = fma_(-dt, g1 + Gp[1], q.M);
-        o2.N = fma_(-dt, g2 + Gp[2], q.N);
-        if constexpr (AXI && !GHOST) geometric_half_step(o2, hdt * rinv_at<T>(d, vr));
-        return o2;
+        return x1_sweep<T, AXI && !GHOST, !GHOST>(q, dt, beta, hdt * (AXI && !GHOST ? rinv_at<T>(d, vr) : T(0)), xacc);
     };
     auto xsweep = [&](int vr, S ra, S rb, S rc) -> Cell<T> {
         Cell<T> q;
@@ -956,16 +1180,8 @@ __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, cons
     // that went through the same first fractional step as the interior
     auto xsweep_taylor_ghost = [&](int vr) -> Cell<T> {
         double R, M, N;
-        taylor_at(d, tx0, scol + 0.5, vr + 0.5, tn, R, M, N);
+        taylor_at(d, taylor_x0(d, at.x_off), opaque(xs.scol) + 0.5, vr + 0.5, tn, R, M, N);
         return xsweep_core(Flag<true>{}, vr, Cell<T>{(T)R, (T)M, (T)N});
-    };
-
-    // analytic (Taylor) velocities of a ghost cell
-    auto taylor_uv = [&](double x, double y, T& uu, T& vv) {
-        double R, M, N;
-        taylor_at(d, tx0, x, y, tn, R, M, N);
-        uu = (T)(M / (1.0 + R));
-        vv = (T)(N / (1.0 + R));
     };
 
     const int vfirst = rs;
@@ -1007,55 +1223,15 @@ __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, cons
             T uxl = from_lo(in.us), vxl = from_lo(in.vs);
             T uxr = from_hi(in.us), vxr = from_hi(in.vs);
             T ubl = in.ub, vbl = in.vb, uab = un, vab = vn;
-            if (EDGE) {
-                if (ghost_lo) {
-                    const int b = d.bc[0];
-                    if (b == BC_REFLECT) { uxl = -in.us; vxl = in.vs; }
-                    else if (b == BC_TAYLOR) taylor_uv(-0.5, j + 0.5, uxl, vxl);
-                    else if (b == BC_SOURCE && j + 0.5 <= src_clk.ap) {
-                        T R, M, N;
-                        source_at<T>(d, j, src_clk, R, M, N);
-                        const T ir = rcp(T(1) + R);
-                        uxl = M * ir; vxl = N * ir;
-                    } else { uxl = in.us; vxl = in.vs; }
-                }
-                if (ghost_hi) {
-                    const int b = d.bc[1];
-                    if (b == BC_REFLECT) { uxr = -in.us; vxr = in.vs; }
-                    else if (b == BC_TAYLOR) taylor_uv(nx + 0.5, j + 0.5, uxr, vxr);
-                    else { uxr = in.us; vxr = in.vs; }
-                }
-            }
+            if (EDGE)
+                x_ghost_uv(d, xs, tab, tab.per != 0 ? side_slot(j) : 0, j + 0.5 <= src_clk.ap, in.us, in.vs, uxl, vxl,
+                           uxr, vxr);
             if constexpr (!LEAN) {
-                if (!pery && j == 0) {
-                    const int b = d.bc[2];
-                    if (b == BC_REFLECT) { ubl = in.us; vbl = -in.vs; }
-                    else if (b == BC_TAYLOR) taylor_uv(col + 0.5, -0.5, ubl, vbl);
-                    else { ubl = in.us; vbl = in.vs; }
-                }
-                if (!pery && j == ny - 1) {
-                    const int b = d.bc[3];
-                    if (b == BC_REFLECT) { uab = in.us; vab = -in.vs; }
-                    else if (b == BC_TAYLOR) taylor_uv(col + 0.5, ny + 0.5, uab, vab);
-                    else { uab = in.us; vab = in.vs; }
-                }
+                if (!pery) y_ghost_uv(d, at.x_off, tn, col, j, in.us, in.vs, ubl, vbl, uab, vab);
             }
-            const T lapu = fma_(T(-4), in.us, (uxl + uxr) + (ubl + uab));
-            const T lapv = fma_(T(-4), in.vs, (vxl + vxr) + (vbl + vab));
             const T oRv = in.qs.R;
             T oMv, oNv;
-            if constexpr (AXI) {
-                // cylindrical vector Laplacian: + (1/r) d/dr of each velocity, - v/r^2
-                const T ir = rinv_at<T>(d, j);
-                const T dur = T(0.5) * (uab - ubl), dvr = T(0.5) * (vab - vbl);
-                const T k = dt * delta;
-                oMv = fma_(k, fma_(dur, ir, lapu), in.qs.M);
-                oNv = fma_(k, fma_(-in.vs, ir * ir, fma_(dvr, ir, lapv)), in.qs.N);
-            } else {
-                const T k = dt * delta;
-                oMv = fma_(k, lapu, in.qs.M);
-                oNv = fma_(k, lapv, in.qs.N);
-            }
+            source_row<T, AXI>(d, j, dt * delta, in.qs, in.us, in.vs, uxl, vxl, uxr, vxr, ubl, vbl, uab, vab, oMv, oNv);
             if constexpr (LEAN) {
                 const int so = (j - rs) * pb;
                 bst(oR, vst, so, C::st(oRv, is0));
@@ -1189,7 +1365,7 @@ __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, cons
     // x1 interface of lane l: between columns col-1 and col (lane 0 has no
     // left neighbour); x2 interfaces: lanes whose x1-swept values are exact.
     const bool cnt_x = lane >= 1 && (perx || (col >= 0 && col <= nx));
-    const bool cnt_y = lane >= 2 && lane <= WAVE - 3 && real_col;
+    const bool cnt_y = lane >= 2 && lane <= WAVE - 3 && xs.real_col;
     T sx, sy;
     bool hx, hy, fx, fy;
     xacc.finish(cnt_x, sx, hx, fx);
@@ -1223,6 +1399,327 @@ __device__ __forceinline__ void march_tile(const SimDesc& d, int strip, int seg,
         if (lean) march<S, T, AXI, true, true>(d, strip, seg, at);
         else march<S, T, AXI, true, false>(d, strip, seg, at);
     }
+}
+
+// ---------------------------------------------------------------------------
+// The fused step of one block tile: BLOCK_ROWS wavefronts, one row each.
+//
+// march_tile gives a wavefront a segment to itself and every row depends on
+// the one before it through registers: a row takes about 1.1 us (FP64) or
+// 0.75 us (FP32) however idle the chip is, and a segment cannot have fewer
+// than 7 rows.  Here the rows of a strip are dealt to the wavefronts of one
+// block, row v to wavefront (v - vfirst) mod BLOCK_ROWS, and the stages of
+// the step that need other rows meet in LDS with a barrier between them:
+//   A  x1 sweep of row v                                  -> cell
+//   B  x2 interface v - 1/2 (cells v - 1, v)              -> waves
+//   C  limited correction at v - 3/2 (waves of v - 5/2,
+//      v - 3/2, v - 1/2), lower flux into row v - 1       -> partial row
+//   D  row v - 2 completed, its velocities                -> x2-swept row
+//   E  source of row v - 3 (x2-swept rows v - 4 .. v - 2), store
+// so 16 rows take little longer than one, a SIMD always has four waves, and a
+// tall tile goes on with the next 16 rows: what its first rows need of the
+// batch before (one cell, two interfaces, one partial row, two x2-swept rows)
+// is kept in LDS, and nothing is recomputed inside a tile.  A tile of n output
+// rows pushes rows r0 - 3 .. r1 + 2, n + 6 in all.
+// Every row takes the same path: a ghost row of a y side is the x1 sweep of
+// the row its side rule names (mirrored rows with N negated), which is that
+// rule applied to the x1-swept state, and with analytic data the x1 sweep of
+// the data.  The arithmetic of a cell is that of march_tile, operation for
+// operation, so results do not depend on which of the two runs.
+// ---------------------------------------------------------------------------
+constexpr int BLOCK_ROWS = 8;
+constexpr int CARRY_ROWS = 4 + 2 * 8 + 3 + 7;
+
+template <typename T> struct BlockShare {
+    T cell[3][BLOCK_ROWS][WAVE];      // A -> B: x1-swept cells; C -> D: partial rows
+    T wave[8][BLOCK_ROWS][WAVE];      // B -> C: waves; D -> E: x2-swept cells and velocities
+    // of the batch before (row numbers relative to the batch's first row b)
+    T cell_c[4][WAVE];                // cell b - 1 and the density of b - 2
+    T wave_c[2][8][WAVE];             // interfaces b - 3/2 and b - 5/2
+    T part_c[3][WAVE];                // partial row b - 2
+    T done_c[2][7][WAVE];             // x2-swept row b - 3, velocities of b - 4; by batch parity
+    T smax[BLOCK_ROWS];
+    unsigned flags[BLOCK_ROWS];
+};
+
+// begin(at): the attempt's clock state; false when no step is owed.
+template <typename S, typename T, int AXI, bool EDGE, typename Begin>
+__device__ __forceinline__ void block_march(const SimDesc& d, int strip, int r0, int r1, BlockShare<T>& sh,
+                                            const Begin& begin)
+{
+    using C = Codec<S, T>;
+    constexpr int W = BLOCK_ROWS;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // this wavefront's place in a batch
+    const int nx = d.nx, ny = d.ny;
+    const int col = strip * OUTW - HALO + lane;
+    const size_t pitch = (size_t)d.pitch;
+    const bool perx = d.bc[0] == BC_PERIODIC;
+    const bool pery = d.bc[2] == BC_PERIODIC;
+    const XSide<T> xs = x_side<T, EDGE>(d, col);
+    const bool out_lane = lane >= HALO && lane < WAVE - HALO && col < nx;
+    const int vfirst = r0 - HALO, vlast = r1 + HALO - 1;
+    // the stored row that row v of the x1-swept state comes from; flip: N
+    // mirrored; data: analytic ghost row
+    auto row_of = [&](int v, bool& flip, bool& data) -> int {
+        flip = data = false;
+        int r = v;
+        if (v < 0) {
+            flip = d.bc[2] == BC_REFLECT;
+            data = d.bc[2] == BC_TAYLOR;
+            r = pery ? v + ny : flip ? -1 - v : 0;
+        } else if (v >= ny) {
+            flip = d.bc[3] == BC_REFLECT;
+            data = d.bc[3] == BC_TAYLOR;
+            r = pery ? v - ny : flip ? 2 * ny - 1 - v : ny - 1;
+        }
+        return min(max(r, 0), ny - 1);
+    };
+    auto load_row = [&](const void* buf, int r, S& a, S& b, S& c) {
+        const S* p = (const S*)buf + (size_t)r * pitch;
+        a = p[xs.scol];
+        b = (p + d.plane)[xs.scol];
+        c = (p + 2 * d.plane)[xs.scol];
+    };
+
+    // The first rows are on their way from both buffers before the clock says
+    // which one is current: the two round trips overlap.
+    bool flip, data;
+    S la, lb, lc, ma, mb, mc;
+    {
+        const int r = row_of(min(vfirst + i, vlast), flip, data);
+        load_row(d.buf[0], r, la, lb, lc);
+        load_row(d.buf[1], r, ma, mb, mc);
+    }
+    // the first batch's predecessors are the zeroed carry of march_tile
+    T (*carry)[WAVE] = sh.cell_c;                      // cell_c .. done_c[0], row by row
+    for (int k = i; k < CARRY_ROWS; k += W) carry[k][lane] = T(0);
+
+    Attempt at;
+    if (!begin(at)) return;                            // the whole block
+    const double tn = at.t;
+    const T dt = (T)at.dt;
+    const T hdt = T(0.5) * dt;
+    const T beta = (T)d.beta;
+    const T delta = (T)d.delta;
+    const void* in = d.buf[at.cur];
+    S* __restrict__ outR = (S*)d.buf[at.cur ^ 1];
+    S* __restrict__ outM = outR + d.plane;
+    S* __restrict__ outN = outM + d.plane;
+    if (at.cur != 0) { la = ma; lb = mb; lc = mc; }
+    Cell<T> qn0{C::ld(la, d.scale[0]), C::ld(lb, d.scale[1]), C::ld(lc, d.scale[2])};    // Q^n of the row to come
+    SourceClock sc = {0.0, 0.0, 0.0, -1.0};
+    if (EDGE && d.bc[0] == BC_SOURCE) sc = source_clock(d, tn);
+    Cfl<T> xacc, yacc;
+
+    SideTable<T> tab = side_table<T, EDGE>(d, sc, strip, pery ? 0 : max(r0 - HALO, 0));
+    int par = 0, tslot = 0;
+#pragma unroll 1
+    for (int base = vfirst; base <= vlast; base += W, par ^= 1, ++tslot) {
+        const int v = base + i;
+        const bool act = v <= vlast;                   // the same for the whole wavefront
+        const bool more = base + W <= vlast;           // another batch follows
+        Cell<T> q{T(0), T(0), T(0)};
+        // ---- A ----
+        if (act) {
+            const int r = row_of(v, flip, data);
+            q = qn0;
+            int vr = r;
+            if (data) {
+                double R, M, N;
+                taylor_at(d, taylor_x0(d, at.x_off), opaque(xs.scol) + 0.5, v + 0.5, tn, R, M, N);
+                q = Cell<T>{(T)R, (T)M, (T)N};
+                vr = v;
+            }
+            if (EDGE) {
+                q.M *= xs.msign;
+                if (tab.per != 0) {
+                    // slots 0 .. half - 1: this wavefront's rows of the batches
+                    // from here on, the others: the rows whose source it takes
+                    if (tslot == tab.slots() / 2) tslot = 0;
+                    if (tslot == 0) {
+                        const int half = tab.slots() / 2, sl = tab.slot_of(lane);
+                        bool f2, d2;
+                        const int va = min(v + W * sl, vlast), ra = row_of(va, f2, d2);
+                        side_fill(d, sc, at.x_off, tn, sl < half ? (d2 ? va : ra) : v - HALO + W * (sl - half), tab);
+                    }
+                    side_cell(d, xs, tab, tslot, col, (unsigned)vr < (unsigned)ny && vr + 0.5 <= sc.ap, q);
+                }
+            }
+            // an analytic ghost row takes no geometric term (hr = 0) and its
+            // interfaces stay out of the CFL maximum
+            const Cfl<T> before = xacc;
+            T hr = T(0);
+            if constexpr (AXI) hr = data ? T(0) : hdt * rinv_at<T>(d, r);
+            q = x1_sweep<T, AXI != 0, true>(q, dt, beta, hr, xacc);
+            if (data) xacc = before;
+            if (flip) q.N = -q.N;
+            sh.cell[0][i][lane] = q.R;
+            sh.cell[1][i][lane] = q.M;
+            sh.cell[2][i][lane] = q.N;
+            if (more) {
+                bool f2, d2;
+                load_row(in, row_of(min(v + W, vlast), f2, d2), la, lb, lc);
+            }
+        }
+        __syncthreads();
+        // ---- B ----
+        Cell<T> ql{T(0), T(0), T(0)};                  // row v - 1
+        Wave<T> wB{};
+        if (act) {
+            T Rl2;                                     // density of row v - 2
+            if (i >= 1) ql = Cell<T>{sh.cell[0][i - 1][lane], sh.cell[1][i - 1][lane], sh.cell[2][i - 1][lane]};
+            else ql = Cell<T>{sh.cell_c[0][lane], sh.cell_c[1][lane], sh.cell_c[2][lane]};
+            Rl2 = i >= 2 ? sh.cell[0][i - 2][lane] : i == 1 ? sh.cell_c[0][lane] : sh.cell_c[3][lane];
+            // velocities of a row come with the reciprocal of the interface
+            // below it (rcp_pair), for row v - 1 as its own wavefront forms them
+            const T Sr = ql.R + q.R;
+            T ir, h, irl, hl;
+            rcp_pair(T(1) + q.R, T(2) + Sr, ir, h);
+            rcp_pair(T(1) + ql.R, T(2) + (Rl2 + ql.R), irl, hl);
+            const T u = q.M * ir, vv = q.N * ir, ul = ql.M * irl, vl = ql.N * irl;
+            T D;
+            const T spd = roe_sh(ql.R, ql.N, ql.M, vl, ul, q.R, q.N, q.M, vv, u, beta, Sr, h, wB, D);
+            if (v > vfirst && (pery || (v >= 0 && v <= ny))) yacc.add(spd, D);
+            sh.wave[0][i][lane] = wB.s1; sh.wave[1][i][lane] = wB.s2; sh.wave[2][i][lane] = wB.s3;
+            sh.wave[3][i][lane] = wB.a1; sh.wave[4][i][lane] = wB.a2; sh.wave[5][i][lane] = wB.a3;
+            sh.wave[6][i][lane] = wB.r1; sh.wave[7][i][lane] = wB.r2;
+        }
+        __syncthreads();
+        // ---- C ----
+        T Gm[3] = {T(0), T(0), T(0)};
+        Cell<T> part{T(0), T(0), T(0)};
+        if (more) {                                    // cells have been read: keep the last ones
+            if (i == W - 1) { sh.cell_c[0][lane] = q.R; sh.cell_c[1][lane] = q.M; sh.cell_c[2][lane] = q.N; }
+            if (i == W - 2) sh.cell_c[3][lane] = q.R;
+        }
+        if (act) {
+            auto wave_at = [&](int k) -> Wave<T> {     // interface k places below this wavefront's
+                const T* p = i >= k ? &sh.wave[0][i - k][lane] : &sh.wave_c[k - i - 1][0][lane];
+                const int st = i >= k ? BLOCK_ROWS * WAVE : WAVE;
+                return Wave<T>{p[0], p[st], p[2 * st], p[3 * st], p[4 * st], p[5 * st], p[6 * st], p[7 * st]};
+            };
+            const Wave<T> wA = wave_at(1), wL = wave_at(2);
+            T dlo[3], dhi[3], t0[3], t1[3];
+            wave_cross(wL, wA, dlo, t0);
+            wave_cross(wA, wB, t1, dhi);
+            T Gp[3];
+            hr_split(wA, dlo, dhi, dt, Gm, Gp);
+            part.R = fma_(-dt, Gp[0], ql.R);
+            part.N = fma_(-dt, Gp[1], ql.N);
+            part.M = fma_(-dt, Gp[2], ql.M);
+            sh.cell[0][i][lane] = part.R;
+            sh.cell[1][i][lane] = part.M;
+            sh.cell[2][i][lane] = part.N;
+        }
+        __syncthreads();
+        // ---- D ----
+        Cell<T> qn{T(0), T(0), T(0)};
+        T un = T(0), vn = T(0);
+        if (more && i >= W - 2) {                      // waves have been read: keep the last two
+            T* p = &sh.wave_c[W - 1 - i][0][lane];
+            p[0] = wB.s1; p[WAVE] = wB.s2; p[2 * WAVE] = wB.s3; p[3 * WAVE] = wB.a1; p[4 * WAVE] = wB.a2;
+            p[5 * WAVE] = wB.a3; p[6 * WAVE] = wB.r1; p[7 * WAVE] = wB.r2;
+        }
+        if (act) {
+            Cell<T> pl;                                // partial row v - 2
+            if (i >= 1) pl = Cell<T>{sh.cell[0][i - 1][lane], sh.cell[1][i - 1][lane], sh.cell[2][i - 1][lane]};
+            else pl = Cell<T>{sh.part_c[0][lane], sh.part_c[1][lane], sh.part_c[2][lane]};
+            qn.R = fma_(-dt, Gm[0], pl.R);
+            qn.N = fma_(-dt, Gm[1], pl.N);
+            qn.M = fma_(-dt, Gm[2], pl.M);
+            if constexpr (AXI) geometric_half_step(qn, hdt * rinv_at<T>(d, v - 2));
+            const T irn = rcp(T(1) + qn.R);
+            un = qn.M * irn;
+            vn = qn.N * irn;
+            sh.wave[0][i][lane] = qn.R; sh.wave[1][i][lane] = qn.M; sh.wave[2][i][lane] = qn.N;
+            sh.wave[3][i][lane] = un; sh.wave[4][i][lane] = vn;
+        }
+        __syncthreads();
+        // ---- E ----
+        if (more) {
+            // partial rows have been read: keep the last; the x2-swept rows go
+            // to the other parity, this batch's may still be read
+            if (i == W - 1) {
+                sh.part_c[0][lane] = part.R; sh.part_c[1][lane] = part.M; sh.part_c[2][lane] = part.N;
+                T* p = &sh.done_c[par ^ 1][0][lane];
+                p[0] = qn.R; p[WAVE] = qn.M; p[2 * WAVE] = qn.N; p[3 * WAVE] = un; p[4 * WAVE] = vn;
+            } else if (i == W - 2) {
+                sh.done_c[par ^ 1][5][lane] = un;
+                sh.done_c[par ^ 1][6][lane] = vn;
+            }
+        }
+        // the next row's loads are waited for here, ahead of this row's stores:
+        // loads and stores share one in-order counter, and a wait after the
+        // stores would be a wait for them
+        if (more) {
+            qn0 = Cell<T>{C::ld(la, d.scale[0]), C::ld(lb, d.scale[1]), C::ld(lc, d.scale[2])};
+            asm volatile("" : "+v"(qn0.R), "+v"(qn0.M), "+v"(qn0.N));
+        }
+        const int j = v - 3;
+        if (act && j >= r0) {
+            const T* p = i >= 1 ? &sh.wave[0][i - 1][lane] : &sh.done_c[par][0][lane];
+            const int st = i >= 1 ? BLOCK_ROWS * WAVE : WAVE;
+            const Cell<T> qs{p[0], p[st], p[2 * st]};
+            const T us = p[3 * st], vs = p[4 * st];
+            T ubl, vbl;
+            if (i >= 2) { ubl = sh.wave[3][i - 2][lane]; vbl = sh.wave[4][i - 2][lane]; }
+            else if (i == 1) { ubl = sh.done_c[par][3][lane]; vbl = sh.done_c[par][4][lane]; }
+            else { ubl = sh.done_c[par][5][lane]; vbl = sh.done_c[par][6][lane]; }
+            T uab = un, vab = vn;
+            T uxl = from_lo(us), vxl = from_lo(vs), uxr = from_hi(us), vxr = from_hi(vs);
+            if (EDGE)
+                x_ghost_uv(d, xs, tab, tab.slots() / 2 + tslot, j + 0.5 <= sc.ap, us, vs, uxl, vxl, uxr, vxr);
+            if (!pery) y_ghost_uv(d, at.x_off, tn, col, j, us, vs, ubl, vbl, uab, vab);
+            T oM, oN;
+            source_row<T, AXI>(d, j, dt * delta, qs, us, vs, uxl, vxl, uxr, vxr, ubl, vbl, uab, vab, oM, oN);
+            if (out_lane) {
+                const size_t o = (size_t)j * pitch;
+                (outR + o)[col] = C::st(qs.R, d.inv_scale[0]);
+                (outM + o)[col] = C::st(oM, d.inv_scale[1]);
+                (outN + o)[col] = C::st(oN, d.inv_scale[2]);
+            }
+        }
+    }
+
+    // ---- CFL maximum: over the wavefront, then the block, one atomic ----
+    const bool cnt_x = lane >= 1 && (perx || (col >= 0 && col <= nx));
+    const bool cnt_y = lane >= 2 && lane <= WAVE - 3 && xs.real_col;
+    T sx, sy;
+    bool hx, hy, fx, fy;
+    xacc.finish(cnt_x, sx, hx, fx);
+    yacc.finish(cnt_y, sy, hy, fy);
+    T m = max_(sx, sy);
+    for (int off = 32; off >= 1; off >>= 1) m = max_(m, perm(m, lane ^ off));
+    const bool anyh = __any(hx || hy), anyf = __any(fx || fy);
+    if (lane == 0) {
+        sh.smax[i] = m;
+        sh.flags[i] = (anyh ? FLAG_NONHYP : 0u) | (anyf ? FLAG_NONFINITE : 0u);
+    }
+    __syncthreads();
+    if (i == 0) {
+        m = sh.smax[lane & (W - 1)];
+        unsigned fl = sh.flags[lane & (W - 1)];
+        for (int off = W / 2; off >= 1; off >>= 1) {
+            m = max_(m, perm(m, lane ^ off));
+            fl |= (unsigned)__builtin_amdgcn_ds_bpermute((lane ^ off) << 2, (int)fl);
+        }
+        if (lane == 0) {
+            atomicMax(at.smax, (unsigned long long)__double_as_longlong(cfl_speed<T>(m)));
+            if (fl) atomicOr(at.flags, fl);
+        }
+    }
+}
+
+template <typename S, typename T, int AXI, typename Begin>
+__device__ __forceinline__ void block_tile(const SimDesc& d, int strip, int seg, int rows, BlockShare<T>& sh,
+                                           const Begin& begin)
+{
+    const int c0 = strip * OUTW;
+    const bool interior = d.bc[0] == BC_PERIODIC || (c0 - HALO >= 0 && c0 + OUTW + HALO - 1 <= d.nx - 1);
+    const int r0 = seg * rows, r1 = min(r0 + rows, d.ny);
+    if (interior) block_march<S, T, AXI, false>(d, strip, r0, r1, sh, begin);
+    else block_march<S, T, AXI, true>(d, strip, r0, r1, sh, begin);
 }
 
 }  // namespace fvna

@@ -638,24 +638,65 @@ static void set_segments(SimDesc& d, int tr, bool short_edges = true)
 // grid's wavefronts fill every resident slot of the device (CUs x 4 SIMDs x
 // the occupancy the step kernel is compiled for) in one round without
 // spilling a few into a second round, and never fewer than 16 rows (the six
-// warm-up rows of a segment are redundant work).
+// warm-up rows of a segment are redundant work).  FP32 segments that would
+// come out shorter than 32 rows are made for half the slots instead: at three
+// wavefronts per SIMD their warm-up rows and their start cost more than the
+// third wavefront brings (us per step, slots full / half: 1500^2 54.8 / 42.1,
+// 2000^2 66.2 / 57.3; 2500^2, 38 rows, 79.5 / 84).
 int default_tile_rows(const fvna_params* p, int cu_count)
 {
+    const long long strips = (p->nx + OUTW - 1) / OUTW;
+    auto rows_for = [&](long long slots) -> long long {
+        const long long per_strip = std::max(1ll, slots / strips);
+        long long tr = (p->ny + per_strip - 1) / per_strip;
+        tr = std::max(16ll, std::min(tr, 65536ll));
+        // shorter first and last segments: the smallest height whose segments
+        // still fit the slots (at most per_strip of them)
+        if (FVNA_EDGE_PERMILLE < 1000 && per_strip >= 3) {
+            const double f = FVNA_EDGE_PERMILLE / 1000.0;
+            long long t2 = std::max(16ll, (long long)std::ceil(p->ny / (per_strip - 2 + 2 * f)));
+            while (t2 < 65536 && segments_of(p->ny, (int)t2).segs > per_strip) ++t2;
+            tr = t2;
+        }
+        return tr;
+    };
     const int waves_per_simd = p->precision == FVNA_F64 ? Occupancy<double>::waves : Occupancy<float>::waves;
     const long long slots = (long long)std::max(cu_count, 1) * 4 * waves_per_simd;
-    const long long strips = (p->nx + OUTW - 1) / OUTW;
-    const long long per_strip = std::max(1ll, slots / strips);
-    long long tr = (p->ny + per_strip - 1) / per_strip;
-    tr = std::max(16ll, std::min(tr, 65536ll));
-    // shorter first and last segments: the smallest height whose segments
-    // still fit the slots (at most per_strip of them)
-    if (FVNA_EDGE_PERMILLE < 1000 && per_strip >= 3) {
-        const double f = FVNA_EDGE_PERMILLE / 1000.0;
-        long long t2 = std::max(16ll, (long long)std::ceil(p->ny / (per_strip - 2 + 2 * f)));
-        while (t2 < 65536 && segments_of(p->ny, (int)t2).segs > per_strip) ++t2;
-        tr = t2;
+    const long long tr = rows_for(slots);
+    return (int)(p->precision != FVNA_F64 && tr < 32 ? rows_for(slots / 2) : tr);
+}
+
+// Block tiles (k_step_block) or wavefront segments (k_step) for a grid whose
+// caller gave no height, and the rows of a block tile.  A block tile of
+// T = BLOCK_ROWS B - 6 rows takes B batches; a CU holds two blocks (LDS and
+// registers).  Measured per batch: 2.85 us FP64, 2.0 us FP32 for a block alone
+// on its CU, 1.55 times that for two together, and 4.5 us per launch, which
+// with the blocks in rounds of two per CU gives the time of every T within
+// about 10%; the T of least time is taken.  Against it stands k_step's time on
+// large grids, 24 us + 13.1 ps per cell FP64, 25 us + 7.6 ps FP32 (fitted to
+// 1000^2 .. 4096^2).  The line comes out near 1.6 million cells FP64 and 3
+// million FP32.  Measured us per step, block / k_step at its best height:
+// FP64 96^2 8.4 / 17.2, 360^2 12.5 / 18.6, 1000^2 32.3 / 38.4, 1300^2 46.9 /
+// 45.9, 2000^2 89.5 / 74.0; FP32 360^2 10.6 / 15.3, 1000^2 23.2 / 30.8, 1500^2
+// 40.1 / 42.1, 2000^2 62.0 / 57.3.
+static int block_rows_for(const fvna_params* p, int cu_count)
+{
+    const bool f64 = p->precision == FVNA_F64;
+    const long long strips = (p->nx + OUTW - 1) / OUTW, cus = std::max(cu_count, 1);
+    const double batch = f64 ? 2.85 : 2.0;
+    double best = 1e30;
+    int rows = 0;
+    for (int b = 1;; ++b) {
+        const int t = BLOCK_ROWS * b - 2 * HALO;
+        const long long segs = (p->ny + t - 1) / t, blocks = strips * segs, rest = blocks % (2 * cus);
+        const double rounds = 1.55 * (double)(blocks / (2 * cus)) + (rest > cus ? 1.55 : rest > 0 ? 1.0 : 0.0);
+        const double us = 4.5 + batch * b * rounds;
+        if (us < best) { best = us; rows = t; }
+        if (segs == 1) break;
     }
-    return (int)tr;
+    const double cells = (double)p->nx * (double)p->ny;
+    const double march = f64 ? 24.0 + 13.1e-6 * cells : 25.0 + 7.6e-6 * cells;
+    return best < march ? rows : 0;
 }
 
 int device_cu_count()
@@ -666,7 +707,8 @@ int device_cu_count()
     return n;
 }
 
-// in-process autotune cache keyed by (precision, geometry, nx, ny)
+// in-process autotune cache keyed by (precision, geometry, nx, ny): rows of a
+// wavefront segment, or minus the rows of a block tile
 std::mutex g_tune_mu;
 std::map<std::tuple<int, int, int, int>, int> g_tune;
 
@@ -689,6 +731,11 @@ Launcher make_launcher()
 {
     Launcher L;
     L.step = [](const SimDesc& d, int force, int pos, hipStream_t s) {
+        if (d.block_rows > 0) {
+            const int tiles = d.strips * ((d.ny + d.block_rows - 1) / d.block_rows);
+            hipLaunchKernelGGL((k_step_block<S, T, AXI>), dim3(tiles), dim3(WAVE * BLOCK_ROWS), 0, s, d, force, pos);
+            return;
+        }
         const int tiles = d.strips * d.segs;
         const int blocks = (tiles + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
         hipLaunchKernelGGL((k_step<S, T, AXI>), dim3(blocks), dim3(256), 0, s, d, force, pos);
@@ -904,13 +951,15 @@ fvna_status fvna_create(const fvna_params* p, void* state_a, void* state_b, void
     c->scratch = (char*)scratch;
     c->clk = (Clock*)(c->scratch + OFF_CLOCK);
     c->L = pick_launcher(p->precision, p->geometry);
-    int tr = p->tile_rows;
+    int tr = p->tile_rows, block = 0;
     if (tr == 0) {
         std::lock_guard<std::mutex> g(g_tune_mu);
         auto it = g_tune.find(std::make_tuple(p->precision, p->geometry, p->nx, p->ny));
-        tr = it != g_tune.end() ? it->second : default_tile_rows(p, device_cu_count());
+        block = it == g_tune.end() ? block_rows_for(p, device_cu_count()) : std::max(0, -it->second);
+        tr = it != g_tune.end() && it->second > 0 ? it->second : default_tile_rows(p, device_cu_count());
     }
     fill_desc(c->d, p, state_a, state_b, c->clk, tr);
+    c->d.block_rows = block;
     if (hipGetDevice(&c->device) != hipSuccess ||
         hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) != hipSuccess) {
         delete c;
@@ -1403,7 +1452,7 @@ fvna_status fvna_time_step_kernel(fvna_ctx* c, int32_t reps, double* ms_per_laun
 fvna_status fvna_get_tile_rows(fvna_ctx* c, int32_t* tile_rows)
 {
     if (!c || !tile_rows) return fail(FVNA_E_INVALID, "NULL argument");
-    *tile_rows = c->d.tile_rows;
+    *tile_rows = c->d.block_rows > 0 ? c->d.block_rows : c->d.tile_rows;
     return FVNA_OK;
 }
 
@@ -1424,25 +1473,31 @@ fvna_status fvna_autotune(fvna_ctx* c, int32_t* tile_rows)
         }
     }
     double best = 1e30;
-    int best_tr = c->d.tile_rows;
-    for (int tr : cand) {
-        if (tr > 2 * c->p.ny) continue;
-        set_segments(c->d, tr);
+    int best_tr = c->d.tile_rows, best_block = 0;
+    // (segment height, block tile rows or 0): the default plan's block tiles first
+    std::vector<std::pair<int, int>> plans;
+    if (c->d.block_rows > 0) plans.emplace_back(c->d.tile_rows, c->d.block_rows);
+    for (int tr : cand)
+        if (tr <= 2 * c->p.ny) plans.emplace_back(tr, 0);
+    for (const auto& pl : plans) {
+        set_segments(c->d, pl.first);
+        c->d.block_rows = pl.second;
         double ms = 0.0;
         fvna_status s = fvna_time_step_kernel(c, 1, &ms);       // warm-up
         if (!s) s = fvna_time_step_kernel(c, 5, &ms);
         if (s) return s;
-        if (ms < best) { best = ms; best_tr = tr; }
+        if (ms < best) { best = ms; best_tr = pl.first; best_block = pl.second; }
     }
     set_segments(c->d, best_tr);
+    c->d.block_rows = best_block;
     // the timing launches left this attempt's speeds in the clock; they are
     // exactly what the next real attempt computes, so nothing to undo
     drop_graph(c);
     {
         std::lock_guard<std::mutex> g(g_tune_mu);
-        g_tune[std::make_tuple(c->p.precision, c->p.geometry, c->p.nx, c->p.ny)] = best_tr;
+        g_tune[std::make_tuple(c->p.precision, c->p.geometry, c->p.nx, c->p.ny)] = best_block > 0 ? -best_block : best_tr;
     }
-    if (tile_rows) *tile_rows = best_tr;
+    if (tile_rows) *tile_rows = best_block > 0 ? best_block : best_tr;
     return FVNA_OK;
 }
 

@@ -17,8 +17,6 @@ namespace fvna {
 #endif
 template <typename T> struct Occupancy { static constexpr int waves = sizeof(T) == 8 ? 2 : FVNA_F32_WAVES_PER_SIMD; };
 
-// One attempted step over the whole grid.  force = 1 (timing): run even when
-// no step is owed.
 // Workgroups are handed to the XCDs round-robin (block b to XCD b mod 8,
 // each with its own L2).  Block b is given logical block start(x) + b / 8 of
 // XCD x = b mod 8, so every XCD works on one contiguous run of tiles, which
@@ -34,17 +32,77 @@ __device__ __forceinline__ int xcd_block(int b, int nblocks)
     return x * per + min(x, rem) + k;
 }
 
+// One attempted step over the whole grid.  force = 1 (timing): run even when
+// no step is owed.
 // pos = 0: the attempt runs with the clock as it stands and its CFL maximum
 // goes to the clock (a controller launch decides after it).  pos >= 1 (the
-// attempts of a captured graph after its first): the attempt first takes the
-// decision on the attempt before it itself.  Every wavefront computes it
-// (control_next) from that attempt's clock state -- the clock for pos = 1,
-// shadow copy (pos - 1) mod 2 after -- and its CFL slot (pos - 1) mod 3,
-// none of which this launch writes; the grid's first wavefront stores the
-// result as shadow copy pos mod 2; this attempt's maximum goes to slot
-// pos mod 3.  Every attempt (pos 0 included) clears slot (pos + 1) mod 3
-// for the one after it.  A closing k_ctrl_fold takes the last decision of
-// the graph into the clock.
+// attempts of a run after its first): the attempt first takes the decision on
+// the attempt before it itself.  Every wavefront computes it (control_next)
+// from that attempt's clock state -- the clock for pos = 1, shadow copy
+// (pos - 1) mod 2 after -- and its CFL slot (pos - 1) mod 3, none of which
+// this launch writes; the grid's first wavefront stores the result as shadow
+// copy pos mod 2 when its tile is done (step_end); this attempt's maximum
+// goes to slot pos mod 3.  Every attempt (pos 0 included) clears slot
+// (pos + 1) mod 3 for the one after it.  A closing k_ctrl_fold takes the last
+// decision of the run into the clock.
+//
+// The words are read through the constant address space (scalar loads: no
+// launch reads what it writes), and a wavefront forms only the parts of the
+// decision it needs; the CFL statistics, two divisions more, are formed once,
+// by the wavefront that stores them, after its tile.  With every wavefront
+// forming all of it from vector loads the prologue of a 16-wavefront block
+// took 4000 to 10000 cycles.
+typedef const __attribute__((address_space(4))) Clock* ConstClock;
+typedef const __attribute__((address_space(4))) unsigned long long* ConstU64;
+typedef const __attribute__((address_space(4))) unsigned int* ConstU32;
+
+__device__ __forceinline__ Clock read_clock(const Clock* p)
+{
+    const ConstClock c = (ConstClock)p;
+    Clock h;
+    h.t = c->t; h.dt = c->dt; h.accepted = c->accepted; h.target = c->target; h.rejected = c->rejected;
+    h.attempts = c->attempts; h.status_step = c->status_step; h.smax_bits = 0; h.flags = 0; h.cur = c->cur;
+    h.status = c->status; h.retries = c->retries; h.nu_last = c->nu_last; h.nu_mean = c->nu_mean;
+    h.nu_m2 = c->nu_m2; h.nu_count = c->nu_count; h.x_off = c->x_off; h.pad = 0.0;
+    return h;
+}
+
+// Clock state the attempt at `pos` runs with.
+__device__ __forceinline__ Clock step_clock(const SimDesc& d, int pos)
+{
+    Clock* clk = d.clk;
+    if (pos == 0) return read_clock(clk);
+    const Clock* prev = pos == 1 ? clk : &clock_aux(clk)->shadow[(pos - 1) & 1];
+    unsigned long long* psb;
+    unsigned int* pfl;
+    cfl_slot(clk, (pos - 1) % 3, psb, pfl);
+    return control_next(read_clock(prev), *(ConstU64)psb, *(ConstU32)pfl, d.fixed_dt, d.cfl_target, d.cfl_max,
+                        d.max_retries, 2);
+}
+
+__device__ __forceinline__ bool step_begin(const SimDesc& d, int force, int pos, Attempt& at)
+{
+    const Clock h = step_clock(d, pos);
+    unsigned long long* sb;
+    unsigned int* fl;
+    cfl_slot(d.clk, pos % 3, sb, fl);
+    at = attempt_of(h, sb, fl);
+    return force || (h.status == 0 && h.accepted < h.target);
+}
+
+// By one lane of the grid: this attempt's clock state for the attempt after
+// it, and a cleared CFL slot for that one to accumulate into (slot 1 after an
+// attempt at pos 0).
+__device__ __forceinline__ void step_end(const SimDesc& d, int pos)
+{
+    if (pos >= 1) clock_aux(d.clk)->shadow[pos & 1] = step_clock(d, pos);
+    unsigned long long* nsb;
+    unsigned int* nfl;
+    cfl_slot(d.clk, (pos + 1) % 3, nsb, nfl);
+    *nsb = 0ull;
+    *nfl = 0u;
+}
+
 template <typename S, typename T, int AXI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Occupancy<T>::waves)))
 void k_step(SimDesc d, int force, int pos)
@@ -52,35 +110,26 @@ void k_step(SimDesc d, int force, int pos)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK + wave;
     if (tile >= d.strips * d.segs) return;
-    Clock* clk = d.clk;
-    ClockAux* aux = clock_aux(clk);
     pos = max(pos, 0);
-    Clock h;
-    if (pos == 0) {
-        h = *clk;
-    } else {
-        const Clock& prev = pos == 1 ? *clk : aux->shadow[(pos - 1) & 1];
-        unsigned long long* psb;
-        unsigned int* pfl;
-        cfl_slot(clk, (pos - 1) % 3, psb, pfl);
-        h = control_next(prev, *psb, *pfl, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 2);
-    }
-    // the grid's first wavefront: this attempt's state for the next one, and
-    // a cleared CFL slot for the next one to accumulate into (slot 1 after an
-    // attempt at pos 0, which the others of its graph then follow)
-    if (tile == 0 && (threadIdx.x & (WAVE - 1)) == 0) {
-        if (pos >= 1) aux->shadow[pos & 1] = h;
-        unsigned long long* nsb;
-        unsigned int* nfl;
-        cfl_slot(clk, (pos + 1) % 3, nsb, nfl);
-        *nsb = 0ull;
-        *nfl = 0u;
-    }
-    unsigned long long* sb;
-    unsigned int* fl;
-    cfl_slot(clk, pos % 3, sb, fl);
-    if (!force && (h.status != 0 || h.accepted >= h.target)) return;
-    march_tile<S, T, AXI>(d, tile % d.strips, tile / d.strips, attempt_of(h, sb, fl));
+    Attempt at;
+    if (step_begin(d, force, pos, at)) march_tile<S, T, AXI>(d, tile % d.strips, tile / d.strips, at);
+    if (tile == 0 && (threadIdx.x & (WAVE - 1)) == 0) step_end(d, pos);
+}
+
+// The same attempt over block tiles (one block per tile): small grids, where
+// march_tile would leave most of the chip idle (see block_march).  Whether a
+// step is owed is the same for the whole block: every wavefront decides from
+// the same words.
+template <typename S, typename T, int AXI>
+__global__ __launch_bounds__(WAVE * BLOCK_ROWS) __attribute__((amdgpu_waves_per_eu(4)))
+void k_step_block(SimDesc d, int force, int pos)
+{
+    __shared__ BlockShare<T> sh;
+    const int tile = xcd_block(blockIdx.x, gridDim.x);
+    pos = max(pos, 0);
+    block_tile<S, T, AXI>(d, tile % d.strips, tile / d.strips, d.block_rows, sh,
+                          [&](Attempt& at) { return step_begin(d, force, pos, at); });
+    if (tile == 0 && threadIdx.x == 0) step_end(d, pos);
 }
 
 struct TileRef { int sim, strip, seg, pad; };
