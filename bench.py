@@ -44,19 +44,19 @@ BYTES_PER_CELL = {"f64": 48, "f32": 24, "f32_f16store": 12, "f32_bf16store": 12}
 # after any change they report null until profiled again.
 PMC_SOURCES = ("csrc/fvna_device.hpp", "csrc/fvna_step.hpp", "csrc/fvna_runtime.hip", "build.py")
 _PROFILED = {
-    "csrc/fvna_device.hpp": "e8a79044eebcf6e19e0827735f2385e5190242fcd93d8f0951e51202d2ddb50c",
-    "csrc/fvna_step.hpp": "a9e84437ccfeefe0500bc34f950718571f6c39e84c9e7b8d6134cc1fc4995563",
-    "csrc/fvna_runtime.hip": "0d2f8bb9b9116e5a8e1603e80e57027609bc6f354015411944941212688ed2a5",
+    "csrc/fvna_device.hpp": "3e76f58f56c4e08409f419cb12c92d66809ea16bda2b4404b40fcf8540fd889c",
+    "csrc/fvna_step.hpp": "7cb19305ef45932c928fb8e9459319971a7cb3cf780226a7c8d87fc6e48d1620",
+    "csrc/fvna_runtime.hip": "ce718845ddf48abb486bc5463fe7bf7c4222ebac01bbf312b7c98bddc04e1b1f",
     "build.py": "02eda4061ab4ab18fbd0c2e868524ec4e9acf39f5fa26d0513e48c2fca74259e",
 }
 PMC = {
     # profiles/k_step_f64_gaussian4096.md
-    "k_step<double,double,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 4.1953e+08, "write_bytes": 4.0525e+08,
-                                "valu_lane_ops_per_cell": 399.6, "valu_issue_cycles_per_cell": 26.49,
+    "k_step<double,double,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 4.1995e+08, "write_bytes": 4.0549e+08,
+                                "valu_lane_ops_per_cell": 400.6, "valu_issue_cycles_per_cell": 26.54,
                                 "sources": _PROFILED},
     # profiles/k_step_f32_gaussian4096.md
-    "k_step<float,float,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 2.1497e+08, "write_bytes": 2.0450e+08,
-                              "valu_lane_ops_per_cell": 300.8, "valu_issue_cycles_per_cell": 19.75,
+    "k_step<float,float,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 2.1448e+08, "write_bytes": 2.0345e+08,
+                              "valu_lane_ops_per_cell": 300.6, "valu_issue_cycles_per_cell": 19.74,
                               "sources": _PROFILED},
 }
 
