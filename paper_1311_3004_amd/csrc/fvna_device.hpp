@@ -1442,13 +1442,17 @@ template <typename T> struct BlockShare {
     unsigned flags[BLOCK_ROWS];
 };
 
+// SIDE: 0 the strip touches no physical x side, 1 it does, 2 it touches one with
+// analytic data (kept apart: the data's registers would spill the row loop of
+// the plain edge strips, which a small grid has many of).
 // begin(at): the attempt's clock state; false when no step is owed.
-template <typename S, typename T, int AXI, bool EDGE, typename Begin>
+template <typename S, typename T, int AXI, int SIDE, typename Begin>
 __device__ __forceinline__ void block_march(const SimDesc& d, int strip, int r0, int r1, BlockShare<T>& sh,
                                             const Begin& begin)
 {
     using C = Codec<S, T>;
     constexpr int W = BLOCK_ROWS;
+    constexpr bool EDGE = SIDE != 0, DATA = SIDE == 2;
     const int lane = threadIdx.x & (WAVE - 1);
     const int i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // this wavefront's place in a batch
     const int nx = d.nx, ny = d.ny;
@@ -1509,10 +1513,10 @@ __device__ __forceinline__ void block_march(const SimDesc& d, int strip, int r0,
     if (at.cur != 0) { la = ma; lb = mb; lc = mc; }
     Cell<T> qn0{C::ld(la, d.scale[0]), C::ld(lb, d.scale[1]), C::ld(lc, d.scale[2])};    // Q^n of the row to come
     SourceClock sc = {0.0, 0.0, 0.0, -1.0};
-    if (EDGE && d.bc[0] == BC_SOURCE) sc = source_clock(d, tn);
+    if (DATA && d.bc[0] == BC_SOURCE) sc = source_clock(d, tn);
     Cfl<T> xacc, yacc;
 
-    SideTable<T> tab = side_table<T, EDGE>(d, sc, strip, pery ? 0 : max(r0 - HALO, 0));
+    SideTable<T> tab = side_table<T, DATA>(d, sc, strip, pery ? 0 : max(r0 - HALO, 0));
     int par = 0, tslot = 0;
 #pragma unroll 1
     for (int base = vfirst; base <= vlast; base += W, par ^= 1, ++tslot) {
@@ -1533,7 +1537,7 @@ __device__ __forceinline__ void block_march(const SimDesc& d, int strip, int r0,
             }
             if (EDGE) {
                 q.M *= xs.msign;
-                if (tab.per != 0) {
+                if (DATA && tab.per != 0) {
                     // slots 0 .. half - 1: this wavefront's rows of the batches
                     // from here on, the others: the rows whose source it takes
                     if (tslot == tab.slots() / 2) tslot = 0;
@@ -1718,8 +1722,11 @@ __device__ __forceinline__ void block_tile(const SimDesc& d, int strip, int seg,
     const int c0 = strip * OUTW;
     const bool interior = d.bc[0] == BC_PERIODIC || (c0 - HALO >= 0 && c0 + OUTW + HALO - 1 <= d.nx - 1);
     const int r0 = seg * rows, r1 = min(r0 + rows, d.ny);
-    if (interior) block_march<S, T, AXI, false>(d, strip, r0, r1, sh, begin);
-    else block_march<S, T, AXI, true>(d, strip, r0, r1, sh, begin);
+    const bool data = (c0 - HALO < 0 && (d.bc[0] == BC_TAYLOR || d.bc[0] == BC_SOURCE)) ||
+                      (c0 + OUTW + HALO - 1 > d.nx - 1 && d.bc[1] == BC_TAYLOR);
+    if (interior) block_march<S, T, AXI, 0>(d, strip, r0, r1, sh, begin);
+    else if (!data) block_march<S, T, AXI, 1>(d, strip, r0, r1, sh, begin);
+    else block_march<S, T, AXI, 2>(d, strip, r0, r1, sh, begin);
 }
 
 }  // namespace fvna

@@ -32,33 +32,26 @@ using namespace fvna;
 // ---------------------------------------------------------------------------
 
 // Accept or reject the attempt just made (control_attempt of
-// fvna_device.hpp); one thread per simulation, in its own launch after the
-// step kernel.  (Deciding in the step kernel's last wavefront instead needs an
-// agent-scope release fence in every wavefront, which writes back the L2 and
-// cost more than the launch it saves.)
+// fvna_device.hpp), one thread per simulation.  (Deciding in the step kernel's
+// last wavefront instead needs an agent-scope release fence in every
+// wavefront, which writes back the L2 and cost more than a launch.)
 __device__ __forceinline__ void control(const SimDesc& d)
 {
     control_attempt(d.clk, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 2);
 }
 
-__global__ void k_ctrl(SimDesc d)
-{
-    if (threadIdx.x == 0) control(d);
-}
-
-// Closing decision of a captured graph whose attempts 1 .. last took the one
-// before them in their prologue (k_step, pos >= 1): the decision on attempt
-// `last` from its shadow state and CFL slot goes into the clock, and every
-// CFL slot is cleared for the next graph.
-#ifndef FVNA_FOLD_CONTROL
-#define FVNA_FOLD_CONTROL 1
-#endif
-__global__ void k_ctrl_fold(SimDesc d, int last)
+// Closing decision of a run of attempts 0 .. last, each of which but the first
+// took the decision on the one before it in its prologue (k_step, pos >= 1):
+// the decision on attempt `last` from its clock state (the clock itself for
+// last = 0) and its CFL slot goes into the clock, and every CFL slot is
+// cleared for the next run.  owed: as the attempts got it.
+__global__ void k_ctrl_fold(SimDesc d, int last, long long owed)
 {
     if (threadIdx.x != 0) return;
     Clock* c = d.clk;
     ClockAux* aux = clock_aux(c);
-    const Clock prev = last == 0 ? *c : aux->shadow[last & 1];
+    Clock prev = last == 0 ? *c : aux->shadow[last & 1];
+    if (last == 0) prev.target += owed;
     unsigned long long* sb;
     unsigned int* fl;
     cfl_slot(c, last % 3, sb, fl);
@@ -715,7 +708,7 @@ std::map<std::tuple<int, int, int, int>, int> g_tune;
 }  // namespace
 
 struct Launcher {
-    void (*step)(const SimDesc&, int force, int pos, hipStream_t);
+    void (*step)(const SimDesc&, int force, int pos, long long owed, hipStream_t);
     void (*step_batch)(const SimDesc*, const TileRef*, int ntiles, int force, hipStream_t);
     void (*dry)(const SimDesc&, hipStream_t);
     void (*imp)(const SimDesc&, const double*, int, int, int, double, int, hipStream_t);
@@ -730,15 +723,15 @@ template <typename S, typename T, int AXI>
 Launcher make_launcher()
 {
     Launcher L;
-    L.step = [](const SimDesc& d, int force, int pos, hipStream_t s) {
+    L.step = [](const SimDesc& d, int force, int pos, long long owed, hipStream_t s) {
         if (d.block_rows > 0) {
             const int tiles = d.strips * ((d.ny + d.block_rows - 1) / d.block_rows);
-            hipLaunchKernelGGL((k_step_block<S, T, AXI>), dim3(tiles), dim3(WAVE * BLOCK_ROWS), 0, s, d, force, pos);
+            hipLaunchKernelGGL((k_step_block<S, T, AXI>), dim3(tiles), dim3(WAVE * BLOCK_ROWS), 0, s, d, force, pos, owed);
             return;
         }
         const int tiles = d.strips * d.segs;
         const int blocks = (tiles + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
-        hipLaunchKernelGGL((k_step<S, T, AXI>), dim3(blocks), dim3(256), 0, s, d, force, pos);
+        hipLaunchKernelGGL((k_step<S, T, AXI>), dim3(blocks), dim3(256), 0, s, d, force, pos, owed);
     };
     L.step_batch = [](const SimDesc* descs, const TileRef* tiles, int ntiles, int force, hipStream_t s) {
         const int blocks = (ntiles + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
@@ -835,13 +828,21 @@ struct fvna_ctx {
     double ta_amp_pa = 0.0, ta_x0_m = 0.0;
 };
 
-// One attempt on stream s: the step, then the CFL decision (and the recorder,
-// in the same launch, if any).
-static void launch_attempt(fvna_ctx* c, hipStream_t s)
+// n attempts in a row on stream s.  Attempts after the first take the decision
+// on the one before them in their prologue and one controller closes the run;
+// with a recorder every attempt is followed by the controller that records.
+// owed: steps these attempts add to the clock's target.
+static void launch_attempts(fvna_ctx* c, int n, long long owed, hipStream_t s)
 {
-    c->L.step(c->d, 0, 0, s);
-    if (c->recording) c->L.ctrl_record(c->d, c->rec, s);
-    else hipLaunchKernelGGL(k_ctrl, dim3(1), dim3(64), 0, s, c->d);
+    for (int k = 0; k < n; ++k) {
+        if (c->recording) {
+            c->L.step(c->d, 0, 0, 0, s);
+            c->L.ctrl_record(c->d, c->rec, s);
+        } else {
+            c->L.step(c->d, 0, k, owed, s);
+        }
+    }
+    if (!c->recording && n > 0) hipLaunchKernelGGL(k_ctrl_fold, dim3(1), dim3(64), 0, s, c->d, n - 1, owed);
 }
 
 // Destroy the captured graph after every launch of it already enqueued on the
@@ -860,14 +861,7 @@ static fvna_status build_graph(fvna_ctx* c)
 {
     if (c->exec) return FVNA_OK;
     HIP_TRY(hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
-    if (c->recording || !FVNA_FOLD_CONTROL) {
-        for (int k = 0; k < GRAPH_CHUNK; ++k) launch_attempt(c, c->cap);
-    } else {
-        // attempts 1 .. GRAPH_CHUNK-1 take the decision on the attempt before
-        // them in their prologue; one controller launch closes the graph
-        for (int k = 0; k < GRAPH_CHUNK; ++k) c->L.step(c->d, 0, k, c->cap);
-        hipLaunchKernelGGL(k_ctrl_fold, dim3(1), dim3(64), 0, c->cap, c->d, GRAPH_CHUNK - 1);
-    }
+    launch_attempts(c, GRAPH_CHUNK, 0, c->cap);
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamEndCapture(c->cap, &g));
     c->graph = g;
@@ -1100,13 +1094,16 @@ fvna_status fvna_set_clock(fvna_ctx* c, double t, double dt_next)
     return reset_clock(c, t * p.c0 / p.dx, dt_next > 0 ? dt_next * p.c0 / p.dx : 0.0, h.cur, h.x_off);
 }
 
-// Enqueue exactly `attempts` attempts: whole captured chunks, then single launches.
-static fvna_status enqueue_attempts(fvna_ctx* c, long long attempts)
+// Enqueue exactly `attempts` attempts: whole captured chunks, then single
+// launches.  The graph is captured by the first call that replays it.
+static fvna_status enqueue_attempts(fvna_ctx* c, long long attempts, long long owed = 0)
 {
-    fvna_status s = build_graph(c);
-    if (s) return s;
-    for (long long k = 0; k < attempts / GRAPH_CHUNK; ++k) HIP_TRY(hipGraphLaunch(c->exec, c->stream));
-    for (long long k = 0; k < attempts % GRAPH_CHUNK; ++k) launch_attempt(c, c->stream);
+    if (attempts >= GRAPH_CHUNK) {
+        const fvna_status s = build_graph(c);
+        if (s) return s;
+        for (long long k = 0; k < attempts / GRAPH_CHUNK; ++k) HIP_TRY(hipGraphLaunch(c->exec, c->stream));
+    }
+    launch_attempts(c, (int)(attempts % GRAPH_CHUNK), owed, c->stream);
     HIP_TRY(hipGetLastError());
     return FVNA_OK;
 }
@@ -1116,6 +1113,8 @@ fvna_status fvna_step(fvna_ctx* c, int64_t nsteps)
     if (!c) return fail(FVNA_E_INVALID, "ctx is NULL");
     if (nsteps < 0) return fail(FVNA_E_INVALID, "nsteps must be >= 0");
     if (nsteps == 0) return FVNA_OK;
+    // short runs carry the steps they add in their own launches
+    if (nsteps < GRAPH_CHUNK && !c->recording) return enqueue_attempts(c, nsteps, nsteps);
     hipLaunchKernelGGL(k_bump, dim3(1), dim3(64), 0, c->stream, c->clk, (long long)nsteps);
     HIP_TRY(hipGetLastError());
     return enqueue_attempts(c, nsteps);
@@ -1437,7 +1436,7 @@ fvna_status fvna_time_step_kernel(fvna_ctx* c, int32_t reps, double* ms_per_laun
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
     HIP_TRY(hipEventRecord(e0, c->stream));
-    for (int k = 0; k < reps; ++k) c->L.step(c->d, 1, 0, c->stream);
+    for (int k = 0; k < reps; ++k) c->L.step(c->d, 1, 0, 0, c->stream);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(e1, c->stream));
     HIP_TRY(hipEventSynchronize(e1));

@@ -67,22 +67,24 @@ __device__ __forceinline__ Clock read_clock(const Clock* p)
     return h;
 }
 
-// Clock state the attempt at `pos` runs with.
-__device__ __forceinline__ Clock step_clock(const SimDesc& d, int pos)
+// Clock state the attempt at `pos` runs with; owed: steps requested by this run
+// of attempts and not yet in the clock's target (a launch that adds them to
+// the clock is saved).
+__device__ __forceinline__ Clock step_clock(const SimDesc& d, int pos, long long owed)
 {
     Clock* clk = d.clk;
-    if (pos == 0) return read_clock(clk);
-    const Clock* prev = pos == 1 ? clk : &clock_aux(clk)->shadow[(pos - 1) & 1];
+    Clock h = read_clock(pos <= 1 ? clk : &clock_aux(clk)->shadow[(pos - 1) & 1]);
+    if (pos <= 1) h.target += owed;
+    if (pos == 0) return h;
     unsigned long long* psb;
     unsigned int* pfl;
     cfl_slot(clk, (pos - 1) % 3, psb, pfl);
-    return control_next(read_clock(prev), *(ConstU64)psb, *(ConstU32)pfl, d.fixed_dt, d.cfl_target, d.cfl_max,
-                        d.max_retries, 2);
+    return control_next(h, *(ConstU64)psb, *(ConstU32)pfl, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 2);
 }
 
-__device__ __forceinline__ bool step_begin(const SimDesc& d, int force, int pos, Attempt& at)
+__device__ __forceinline__ bool step_begin(const SimDesc& d, int force, int pos, long long owed, Attempt& at)
 {
-    const Clock h = step_clock(d, pos);
+    const Clock h = step_clock(d, pos, owed);
     unsigned long long* sb;
     unsigned int* fl;
     cfl_slot(d.clk, pos % 3, sb, fl);
@@ -93,9 +95,9 @@ __device__ __forceinline__ bool step_begin(const SimDesc& d, int force, int pos,
 // By one lane of the grid: this attempt's clock state for the attempt after
 // it, and a cleared CFL slot for that one to accumulate into (slot 1 after an
 // attempt at pos 0).
-__device__ __forceinline__ void step_end(const SimDesc& d, int pos)
+__device__ __forceinline__ void step_end(const SimDesc& d, int pos, long long owed)
 {
-    if (pos >= 1) clock_aux(d.clk)->shadow[pos & 1] = step_clock(d, pos);
+    if (pos >= 1) clock_aux(d.clk)->shadow[pos & 1] = step_clock(d, pos, owed);
     unsigned long long* nsb;
     unsigned int* nfl;
     cfl_slot(d.clk, (pos + 1) % 3, nsb, nfl);
@@ -105,15 +107,15 @@ __device__ __forceinline__ void step_end(const SimDesc& d, int pos)
 
 template <typename S, typename T, int AXI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Occupancy<T>::waves)))
-void k_step(SimDesc d, int force, int pos)
+void k_step(SimDesc d, int force, int pos, long long owed)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK + wave;
     if (tile >= d.strips * d.segs) return;
     pos = max(pos, 0);
     Attempt at;
-    if (step_begin(d, force, pos, at)) march_tile<S, T, AXI>(d, tile % d.strips, tile / d.strips, at);
-    if (tile == 0 && (threadIdx.x & (WAVE - 1)) == 0) step_end(d, pos);
+    if (step_begin(d, force, pos, owed, at)) march_tile<S, T, AXI>(d, tile % d.strips, tile / d.strips, at);
+    if (tile == 0 && (threadIdx.x & (WAVE - 1)) == 0) step_end(d, pos, owed);
 }
 
 // The same attempt over block tiles (one block per tile): small grids, where
@@ -122,14 +124,14 @@ void k_step(SimDesc d, int force, int pos)
 // the same words.
 template <typename S, typename T, int AXI>
 __global__ __launch_bounds__(WAVE * BLOCK_ROWS) __attribute__((amdgpu_waves_per_eu(4)))
-void k_step_block(SimDesc d, int force, int pos)
+void k_step_block(SimDesc d, int force, int pos, long long owed)
 {
     __shared__ BlockShare<T> sh;
     const int tile = xcd_block(blockIdx.x, gridDim.x);
     pos = max(pos, 0);
     block_tile<S, T, AXI>(d, tile % d.strips, tile / d.strips, d.block_rows, sh,
-                          [&](Attempt& at) { return step_begin(d, force, pos, at); });
-    if (tile == 0 && threadIdx.x == 0) step_end(d, pos);
+                          [&](Attempt& at) { return step_begin(d, force, pos, owed, at); });
+    if (tile == 0 && threadIdx.x == 0) step_end(d, pos, owed);
 }
 
 struct TileRef { int sim, strip, seg, pad; };
