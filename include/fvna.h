@@ -237,8 +237,9 @@ typedef struct {
 } fvna_window_state;
 
 /* Advance nsteps accepted steps with the moving-domain rule above, updating
- * *st.  Synchronises the stream at every check (once per check_every steps)
- * and returns the first device status that is not FVNA_OK (the steps of the
+ * *st.  The checks and moves are decided on the device; waits for the stream
+ * at the end of the call (and again for steps that rejected attempts left) and
+ * returns the first device status that is not FVNA_OK (the steps of the
  * failing chunk are not all taken).  FVNA_E_INVALID for bad arguments or x
  * sides that cannot move (as fvna_shift). */
 fvna_status fvna_step_window(fvna_ctx* c, const fvna_window* w, fvna_window_state* st, int64_t nsteps);
@@ -246,15 +247,15 @@ fvna_status fvna_step_window(fvna_ctx* c, const fvna_window* w, fvna_window_stat
 /* Recorder of the on-axis quantities of Sec. 4.2 (pressure maxima over the
  * propagation axis, the time series at a probe) without a host round trip per
  * step.  While set, every attempt of fvna_step, fvna_sync and
- * fvna_step_window is followed by a small kernel that, once at least one step
- * has been accepted since fvna_set_recorder,
+ * fvna_step_window is followed by a recording on the device that, once at least
+ * one step has been accepted since fvna_set_recorder,
  *   row_max[x_off + i] = max(row_max[x_off + i], rho'(i, row))  for x_off + i < path_len,
  * with x_off the cells the domain has moved (fvna_shift) since the state was
  * set, and writes t and rho'(probe, row) of the latest accepted step k
  * (counted from 1 at fvna_set_recorder) to probe_t[k - 1], probe_rho[k - 1]
  * for k <= capacity while the probe column is inside the domain.  rho' in
  * kg/m^3 (p' = c0^2 rho'), t in s.  Rejected attempts leave everything as it
- * was (the kernel is idempotent).  The arrays are caller-owned device memory
+ * was (the recording is idempotent).  The arrays are caller-owned device memory
  * and must outlive the recording; the caller initialises row_max (e.g. to
  * -inf) and the probe arrays.  fvna_set_recorder synchronises the stream;
  * NULL stops recording.  fvna_set_state and fvna_set_clock restart the step

@@ -140,6 +140,20 @@ __device__ __forceinline__ void control_attempt(Clock* c, int fixed_dt, double c
 struct CflSlot { unsigned long long smax_bits; unsigned int flags, pad; };
 struct ClockAux { Clock shadow[2]; CflSlot slot[2]; };
 constexpr size_t CLOCK_AUX_OFFSET = 256;           // bytes after the clock
+
+// Moving domain decided on the device (fvna_step_window): the state of the
+// rule, after the clock's copies in the same allocation.
+struct WinState {
+    long long x_off;             // cells the domain has moved under the rule
+    long long phase;             // accepted steps since the last check
+    long long left;              // steps of the call not yet completed
+    long long seg;               // steps of the segment running (up to the next check)
+    int move;                    // columns the next k_shift moves
+    int halted;                  // a move too large was asked for: nothing more runs
+};
+constexpr size_t WIN_OFFSET = 576;
+__device__ __forceinline__ WinState* win_state(Clock* c) { return (WinState*)((char*)c + WIN_OFFSET); }
+
 __device__ __forceinline__ ClockAux* clock_aux(Clock* c)
 {
     return (ClockAux*)((char*)c + CLOCK_AUX_OFFSET);

@@ -105,14 +105,61 @@ __device__ __forceinline__ void step_end(const SimDesc& d, int pos, long long ow
     *nfl = 0u;
 }
 
+// Recorder: after an attempt, the running maximum of rho' along one grid row,
+// kept per column of the path the (possibly moving) domain covers, and rho'
+// and t at one probe column after every accepted step.  Idempotent: after a
+// rejected or empty attempt it sees the state and step count it saw before,
+// so it can follow every attempt without knowing which were accepted.
+struct RecDesc {
+    int on;                     // 0: no recorder
+    int row, probe_col;
+    long long path_len, base, capacity;
+    double* row_max;
+    double* probe_t;
+    double* probe_rho;
+    double rho0, t_unit;
+};
+
+// By one block of n threads: record the state that clock state h describes.
+template <typename S, typename T>
+__device__ __forceinline__ void record_row(const SimDesc& d, const RecDesc& r, const Clock& h, int n)
+{
+    const long long k = h.accepted - r.base - 1;        // index of the latest accepted step
+    if (k < 0) return;
+    const S* R = (const S*)d.buf[h.cur] + (size_t)r.row * d.pitch;
+    for (int i = threadIdx.x; i < d.nx; i += n) {
+        const double rho = (double)Codec<S, T>::ld(R[i], d.scale[0]) * r.rho0;
+        const long long pc = h.x_off + i;
+        if (pc < r.path_len) r.row_max[pc] = fmax(r.row_max[pc], rho);
+        if (pc == r.probe_col && k < r.capacity) {
+            r.probe_t[k] = h.t * r.t_unit;
+            r.probe_rho[k] = rho;
+        }
+    }
+}
+
+// With a recorder the grid has one block more than its tiles need: the last
+// one records the state the decision on the attempt before this one left (its
+// buffer is the one this attempt reads), beside the tiles instead of in a
+// launch of its own after every attempt (7.6 us each).  The closing launch
+// records after the run's last attempt.
+template <typename S, typename T>
+__device__ __forceinline__ bool record_block(const SimDesc& d, const RecDesc& r, int pos, long long owed)
+{
+    if (!r.on || blockIdx.x != gridDim.x - 1) return false;
+    if (pos >= 1) record_row<S, T>(d, r, step_clock(d, pos, owed), blockDim.x);
+    return true;
+}
+
 template <typename S, typename T, int AXI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Occupancy<T>::waves)))
-void k_step(SimDesc d, int force, int pos, long long owed)
+void k_step(SimDesc d, RecDesc r, int force, int pos, long long owed)
 {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK + wave;
-    if (tile >= d.strips * d.segs) return;
     pos = max(pos, 0);
+    if (record_block<S, T>(d, r, pos, owed)) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = xcd_block(blockIdx.x, gridDim.x - r.on) * WAVES_PER_BLOCK + wave;
+    if (tile >= d.strips * d.segs) return;
     Attempt at;
     if (step_begin(d, force, pos, owed, at)) march_tile<S, T, AXI>(d, tile % d.strips, tile / d.strips, at);
     if (tile == 0 && (threadIdx.x & (WAVE - 1)) == 0) step_end(d, pos, owed);
@@ -124,11 +171,12 @@ void k_step(SimDesc d, int force, int pos, long long owed)
 // the same words.
 template <typename S, typename T, int AXI>
 __global__ __launch_bounds__(WAVE * BLOCK_ROWS) __attribute__((amdgpu_waves_per_eu(4)))
-void k_step_block(SimDesc d, int force, int pos, long long owed)
+void k_step_block(SimDesc d, RecDesc r, int force, int pos, long long owed)
 {
     __shared__ BlockShare<T> sh;
-    const int tile = xcd_block(blockIdx.x, gridDim.x);
     pos = max(pos, 0);
+    if (record_block<S, T>(d, r, pos, owed)) return;
+    const int tile = xcd_block(blockIdx.x, gridDim.x - r.on);
     block_tile<S, T, AXI>(d, tile % d.strips, tile / d.strips, d.block_rows, sh,
                           [&](Attempt& at) { return step_begin(d, force, pos, owed, at); });
     if (tile == 0 && threadIdx.x == 0) step_end(d, pos, owed);
