@@ -188,6 +188,22 @@ __device__ __forceinline__ Attempt attempt_of(const Clock& h, unsigned long long
     return Attempt{uniform(h.t), uniform(h.dt), uniform(h.x_off), uniform(h.cur), sb, fl};
 }
 
+// Raise an attempt's largest wave speed and failure flags (one lane).  Atomics
+// on one word are taken one at a time, about 13 ns each, and a launch whose
+// wavefronts end together waited for all of theirs; most hold no new maximum,
+// so the word is read first (at the agent's scope; it only grows within an
+// attempt, and was cleared by an earlier launch).  us per step, always an
+// atomic / read first: 4096^2 FP32 148 / 135, Taylor sides 2240 x 1200 FP64 75 /
+// 61, 3-D 256^3 FP32 360 / 325, 64^3 67 / 40.  few: so few raise it that the
+// read would take longer than their turns.
+__device__ __forceinline__ void cfl_raise(const Attempt& at, double speed, bool nonhyp, bool nonfin, bool few = false)
+{
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(speed);
+    if (few || bits > __hip_atomic_load(at.smax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(at.smax, bits);
+    const unsigned fl = (nonhyp ? FLAG_NONHYP : 0u) | (nonfin ? FLAG_NONFINITE : 0u);
+    if (fl) atomicOr(at.flags, fl);
+}
+
 // Everything a wavefront needs to know about its simulation.
 struct SimDesc {
     int nx, ny, pitch, strips, segs, tile_rows;
@@ -1388,11 +1404,7 @@ __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, cons
     for (int off = 32; off >= 1; off >>= 1) m = max_(m, perm(m, lane ^ off));
     const bool anyh = __any(hx || hy);
     const bool anyf = __any(fx || fy);
-    if (lane == 0) {
-        atomicMax(at.smax, (unsigned long long)__double_as_longlong(cfl_speed<T>(m)));
-        const unsigned fl = (anyh ? FLAG_NONHYP : 0u) | (anyf ? FLAG_NONFINITE : 0u);
-        if (fl) atomicOr(at.flags, fl);
-    }
+    if (lane == 0) cfl_raise(at, cfl_speed<T>(m), anyh, anyf);
 }
 
 // Interior strips (no ghost column, no x override) take the EDGE = false
@@ -1722,10 +1734,8 @@ __device__ __forceinline__ void block_march(const SimDesc& d, int strip, int r0,
             m = max_(m, perm(m, lane ^ off));
             fl |= (unsigned)__builtin_amdgcn_ds_bpermute((lane ^ off) << 2, (int)fl);
         }
-        if (lane == 0) {
-            atomicMax(at.smax, (unsigned long long)__double_as_longlong(cfl_speed<T>(m)));
-            if (fl) atomicOr(at.flags, fl);
-        }
+        if (lane == 0) cfl_raise(at, cfl_speed<T>(m), (fl & FLAG_NONHYP) != 0, (fl & FLAG_NONFINITE) != 0,
+                                 gridDim.x <= 256);
     }
 }
 

@@ -40,28 +40,6 @@ __device__ __forceinline__ void control(const SimDesc& d)
     control_attempt(d.clk, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 2);
 }
 
-// Closing decision of a run of attempts 0 .. last, each of which but the first
-// took the decision on the one before it in its prologue (k_step, pos >= 1):
-// the decision on attempt `last` from its clock state (the clock itself for
-// last = 0) and its CFL slot goes into the clock, and every CFL slot is
-// cleared for the next run.  owed: as the attempts got it.
-__device__ __forceinline__ Clock fold_decision(const SimDesc& d, int last, long long owed)
-{
-    Clock* c = d.clk;
-    ClockAux* aux = clock_aux(c);
-    Clock prev = last == 0 ? *c : aux->shadow[last & 1];
-    if (last == 0) prev.target += owed;
-    unsigned long long* sb;
-    unsigned int* fl;
-    cfl_slot(c, last % 3, sb, fl);
-    const Clock h = control_next(prev, *sb, *fl, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 2);
-    aux->slot[0].smax_bits = 0ull;
-    aux->slot[0].flags = 0u;
-    aux->slot[1].smax_bits = 0ull;
-    aux->slot[1].flags = 0u;
-    return h;
-}
-
 __global__ void k_ctrl_fold(SimDesc d, int last, long long owed)
 {
     if (threadIdx.x == 0) *d.clk = fold_decision(d, last, owed);
@@ -661,69 +639,80 @@ static void set_segments(SimDesc& d, int tr, bool short_edges = true)
     d.seg_mid = g.mid;
 }
 
-// Rows per wavefront segment when none is given: enough segments that the
-// grid's wavefronts fill every resident slot of the device (CUs x 4 SIMDs x
-// the occupancy the step kernel is compiled for) in one round without
-// spilling a few into a second round, and never fewer than 16 rows (the six
-// warm-up rows of a segment are redundant work).  FP32 segments that would
-// come out shorter than 32 rows are made for half the slots instead: at three
-// wavefronts per SIMD their warm-up rows and their start cost more than the
-// third wavefront brings (us per step, slots full / half: 1500^2 54.8 / 42.1,
-// 2000^2 66.2 / 57.3; 2500^2, 38 rows, 79.5 / 84).
-int default_tile_rows(const fvna_params* p, int cu_count)
+// The plan of a step kernel for a grid whose caller gave no height: rows of a
+// wavefront segment (k_step) or of a block tile (k_step_block), and the time
+// the rule expects of it.
+struct Plan { int rows; double us; };
+
+// Segments: n wavefronts on every SIMD in one round, n up to the occupancy the
+// kernel is compiled for, without spilling a few into a second round.  A row
+// takes longer the more wavefronts share the SIMD, but there are fewer rows;
+// measured, with T rows (T + 6 with the warm-up):
+//   FP64 n = 1: 5 + 0.95 (T + 6) us, n = 2: 5 + 1.53 (T + 6);
+//   FP32 n = 1: 4 + 0.70 (T + 6), n = 2: 4.5 + 0.93 (T + 6), n = 3: 12 + 1.20 (T + 6)
+// (within 8% over 720^2 .. 4096^2), and the least is taken: FP32 1000^2 n = 1
+// 21.8 us per step (n = 2: 28), 2000^2 n = 2 43.2 (n = 1: 66, n = 3: 50), 4096^2
+// n = 3 135 (n = 2: 151).  Never fewer than 8 rows.
+Plan segment_plan(const fvna_params* p, int cu_count)
 {
     const long long strips = (p->nx + OUTW - 1) / OUTW;
     auto rows_for = [&](long long slots) -> long long {
         const long long per_strip = std::max(1ll, slots / strips);
         long long tr = (p->ny + per_strip - 1) / per_strip;
-        tr = std::max(16ll, std::min(tr, 65536ll));
+        tr = std::max(8ll, std::min(tr, 65536ll));
         // shorter first and last segments: the smallest height whose segments
         // still fit the slots (at most per_strip of them)
         if (FVNA_EDGE_PERMILLE < 1000 && per_strip >= 3) {
             const double f = FVNA_EDGE_PERMILLE / 1000.0;
-            long long t2 = std::max(16ll, (long long)std::ceil(p->ny / (per_strip - 2 + 2 * f)));
+            long long t2 = std::max(8ll, (long long)std::ceil(p->ny / (per_strip - 2 + 2 * f)));
             while (t2 < 65536 && segments_of(p->ny, (int)t2).segs > per_strip) ++t2;
             tr = t2;
         }
         return tr;
     };
-    const int waves_per_simd = p->precision == FVNA_F64 ? Occupancy<double>::waves : Occupancy<float>::waves;
-    const long long slots = (long long)std::max(cu_count, 1) * 4 * waves_per_simd;
-    const long long tr = rows_for(slots);
-    return (int)(p->precision != FVNA_F64 && tr < 32 ? rows_for(slots / 2) : tr);
+    static const double f64[][2] = {{5.0, 0.95}, {5.0, 1.53}}, f32[][2] = {{4.0, 0.70}, {4.5, 0.93}, {12.0, 1.20}};
+    const bool d = p->precision == FVNA_F64;
+    const int most = d ? Occupancy<double>::waves : Occupancy<float>::waves;
+    Plan best{0, 1e30};
+    for (int n = 1; n <= most; ++n) {
+        const long long tr = rows_for((long long)std::max(cu_count, 1) * 4 * n);
+        const double* c = d ? f64[n - 1] : f32[n - 1];
+        const double us = c[0] + c[1] * (double)(tr + 2 * HALO);
+        if (us < best.us) best = Plan{(int)tr, us};
+    }
+    return best;
 }
 
-// Block tiles (k_step_block) or wavefront segments (k_step) for a grid whose
-// caller gave no height, and the rows of a block tile.  A block tile of
-// T = BLOCK_ROWS B - 6 rows takes B batches; a CU holds two blocks (LDS and
-// registers).  Measured per batch: 2.85 us FP64, 2.0 us FP32 for a block alone
-// on its CU, 1.55 times that for two together, and 4.5 us per launch, which
-// with the blocks in rounds of two per CU gives the time of every T within
-// about 10%; the T of least time is taken.  Against it stands k_step's time on
-// large grids, 24 us + 13.1 ps per cell FP64, 25 us + 7.6 ps FP32 (fitted to
-// 1000^2 .. 4096^2).  The line comes out near 1.6 million cells FP64 and 3
-// million FP32.  Measured us per step, block / k_step at its best height:
-// FP64 96^2 8.4 / 17.2, 360^2 12.5 / 18.6, 1000^2 32.3 / 38.4, 1300^2 46.9 /
-// 45.9, 2000^2 89.5 / 74.0; FP32 360^2 10.6 / 15.3, 1000^2 23.2 / 30.8, 1500^2
-// 40.1 / 42.1, 2000^2 62.0 / 57.3.
-static int block_rows_for(const fvna_params* p, int cu_count)
+// Block tiles: T = BLOCK_ROWS B - 6 rows take B batches; a CU holds two blocks
+// (LDS and registers).  Measured per batch: 2.85 us FP64, 2.0 us FP32 for a
+// block alone on its CU, 1.55 times that for two together, and 4.5 us per
+// launch, which with the blocks in rounds of two per CU gives the time of
+// every T within about 10%.
+Plan block_plan(const fvna_params* p, int cu_count)
 {
-    const bool f64 = p->precision == FVNA_F64;
     const long long strips = (p->nx + OUTW - 1) / OUTW, cus = std::max(cu_count, 1);
-    const double batch = f64 ? 2.85 : 2.0;
-    double best = 1e30;
-    int rows = 0;
+    const double batch = p->precision == FVNA_F64 ? 2.85 : 2.0;
+    Plan best{0, 1e30};
     for (int b = 1;; ++b) {
         const int t = BLOCK_ROWS * b - 2 * HALO;
         const long long segs = (p->ny + t - 1) / t, blocks = strips * segs, rest = blocks % (2 * cus);
         const double rounds = 1.55 * (double)(blocks / (2 * cus)) + (rest > cus ? 1.55 : rest > 0 ? 1.0 : 0.0);
         const double us = 4.5 + batch * b * rounds;
-        if (us < best) { best = us; rows = t; }
+        if (us < best.us) best = Plan{t, us};
         if (segs == 1) break;
     }
-    const double cells = (double)p->nx * (double)p->ny;
-    const double march = f64 ? 24.0 + 13.1e-6 * cells : 25.0 + 7.6e-6 * cells;
-    return best < march ? rows : 0;
+    return best;
+}
+
+// Rows of a block tile, or 0 for segments: whichever plan expects the shorter
+// step.  The line comes out near half a million cells.  Measured us per step,
+// block tiles / segments: FP64 96^2 8.4 / 17.2, 360^2 12.5 / 20.1, 720^2 22.1 /
+// 21.6, 1300^2 46.4 / 39.1; FP32 360^2 10.6 / 15.5, 720^2 16.9 / 17.3, 1000^2
+// 23.1 / 21.8, 2000^2 60.4 / 43.2.
+static int block_rows_for(const fvna_params* p, int cu_count)
+{
+    const Plan b = block_plan(p, cu_count);
+    return b.us < segment_plan(p, cu_count).us ? b.rows : 0;
 }
 
 int device_cu_count()
@@ -980,7 +969,7 @@ fvna_status fvna_create(const fvna_params* p, void* state_a, void* state_b, void
         std::lock_guard<std::mutex> g(g_tune_mu);
         auto it = g_tune.find(std::make_tuple(p->precision, p->geometry, p->nx, p->ny));
         block = it == g_tune.end() ? block_rows_for(p, device_cu_count()) : std::max(0, -it->second);
-        tr = it != g_tune.end() && it->second > 0 ? it->second : default_tile_rows(p, device_cu_count());
+        tr = it != g_tune.end() && it->second > 0 ? it->second : segment_plan(p, device_cu_count()).rows;
     }
     fill_desc(c->d, p, state_a, state_b, c->clk, tr);
     c->d.block_rows = block;

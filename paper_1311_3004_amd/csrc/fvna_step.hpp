@@ -70,7 +70,9 @@ __device__ __forceinline__ Clock read_clock(const Clock* p)
 // Clock state the attempt at `pos` runs with; owed: steps requested by this run
 // of attempts and not yet in the clock's target (a launch that adds them to
 // the clock is saved).
-__device__ __forceinline__ Clock step_clock(const SimDesc& d, int pos, long long owed)
+// (D: the simulation's descriptor, two- or three-dimensional.)
+template <typename D>
+__device__ __forceinline__ Clock step_clock(const D& d, int pos, long long owed)
 {
     Clock* clk = d.clk;
     Clock h = read_clock(pos <= 1 ? clk : &clock_aux(clk)->shadow[(pos - 1) & 1]);
@@ -82,7 +84,8 @@ __device__ __forceinline__ Clock step_clock(const SimDesc& d, int pos, long long
     return control_next(h, *(ConstU64)psb, *(ConstU32)pfl, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 2);
 }
 
-__device__ __forceinline__ bool step_begin(const SimDesc& d, int force, int pos, long long owed, Attempt& at)
+template <typename D>
+__device__ __forceinline__ bool step_begin(const D& d, int force, int pos, long long owed, Attempt& at)
 {
     const Clock h = step_clock(d, pos, owed);
     unsigned long long* sb;
@@ -95,7 +98,8 @@ __device__ __forceinline__ bool step_begin(const SimDesc& d, int force, int pos,
 // By one lane of the grid: this attempt's clock state for the attempt after
 // it, and a cleared CFL slot for that one to accumulate into (slot 1 after an
 // attempt at pos 0).
-__device__ __forceinline__ void step_end(const SimDesc& d, int pos, long long owed)
+template <typename D>
+__device__ __forceinline__ void step_end(const D& d, int pos, long long owed)
 {
     if (pos >= 1) clock_aux(d.clk)->shadow[pos & 1] = step_clock(d, pos, owed);
     unsigned long long* nsb;
@@ -103,6 +107,29 @@ __device__ __forceinline__ void step_end(const SimDesc& d, int pos, long long ow
     cfl_slot(d.clk, (pos + 1) % 3, nsb, nfl);
     *nsb = 0ull;
     *nfl = 0u;
+}
+
+// Closing decision of a run of attempts 0 .. last, each of which but the first
+// took the decision on the one before it in its prologue (k_step, pos >= 1):
+// the decision on attempt `last` from its clock state (the clock itself for
+// last = 0) and its CFL slot goes into the clock, and every CFL slot is
+// cleared for the next run.  owed: as the attempts got it.
+template <typename D>
+__device__ __forceinline__ Clock fold_decision(const D& d, int last, long long owed)
+{
+    Clock* c = d.clk;
+    ClockAux* aux = clock_aux(c);
+    Clock prev = last == 0 ? *c : aux->shadow[last & 1];
+    if (last == 0) prev.target += owed;
+    unsigned long long* sb;
+    unsigned int* fl;
+    cfl_slot(c, last % 3, sb, fl);
+    const Clock h = control_next(prev, *sb, *fl, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 2);
+    aux->slot[0].smax_bits = 0ull;
+    aux->slot[0].flags = 0u;
+    aux->slot[1].smax_bits = 0ull;
+    aux->slot[1].flags = 0u;
+    return h;
 }
 
 // Recorder: after an attempt, the running maximum of rho' along one grid row,
