@@ -10,21 +10,18 @@
 //               left cell, the neighbour waves and the right flux over DPP
 //               lane shifts, every x1 interface solved once), a register
 //               march along x2 (every x2 interface solved once);
-//   k3_sweep3   x3 sweep: a register march along x3, one lane per column;
-//   k3_source   7-point Laplacian of each velocity component: x3 neighbours
-//               carried in registers, x1 neighbours over DPP, x2 neighbours
-//               loaded;
-//   k3_ctrl     accept or reject (control_attempt), one thread.
-// Three state buffers X0, X1, X2 and the device clock's cur = c.  The source
-// leaves the density as the x3 sweep made it, so a state keeps its density
-// and its momenta in different buffers: density in X[1-c], momenta in X[-c]
-// (indices modulo 3).  The x1-x2 sweep writes all four fields to the third
-// buffer X[2-c]; the x3 sweep writes its density into X[-c] and its momenta
-// into X[1-c] (planes the current state does not use); the source writes the
-// momenta into X[2-c] and no density.  An accepted step advances c by one,
-// which makes exactly these the new state's buffers; a rejected one leaves
-// the current state untouched.  Steps are replayed from a captured HIP graph;
-// the host waits once per fvna3_step call.
+//   k3_sweep3s  x3 sweep and source of one x1-x2 tile: every thread marches
+//               one column along x3 in registers, and the velocities of the
+//               swept planes meet in LDS for the 7-point Laplacian.
+// Three state buffers X0, X1, X2 and the device clock's cur = c in {0, 1}: the
+// state's density is in X[1-c] and its momenta in X[c]; the x1-x2 sweep writes
+// all four fields to X2, and the second kernel writes the new state into the
+// planes the old one does not use (density X[c], momenta X[1-c]).  An accepted
+// step flips c; a rejected one leaves the current state untouched.  The
+// decision on an attempt (accept or reject, the next time step) is taken in
+// the prologues of the attempt after it, as in two dimensions (step_begin).
+// Steps are replayed from a captured HIP graph; the host waits once per
+// fvna3_step call.
 // Ghost values follow the side rule of their axis applied to the state of
 // the stage that needs them (Q^n for x1, the x1-swept state for x2, the
 // x2-swept state for x3, the x3-swept state for the source).
@@ -47,9 +44,9 @@ constexpr int HALO12 = 2;                      // x1 stencil: two interfaces eac
 constexpr int OUT12 = WAVE - 2 * HALO12;       // 60 output columns per x1-x2 wavefront
 
 // Buffer roles for clock cur = c (see the file's header).
-__device__ __forceinline__ int buf_rho(int c) { return c == 0 ? 1 : c == 1 ? 0 : 2; }
-__device__ __forceinline__ int buf_mom(int c) { return c == 0 ? 0 : c == 1 ? 2 : 1; }
-__device__ __forceinline__ int buf_x12(int c) { return c == 0 ? 2 : c == 1 ? 1 : 0; }
+__device__ __forceinline__ int buf_rho(int c) { return c ^ 1; }
+__device__ __forceinline__ int buf_mom(int c) { return c; }
+constexpr int BUF_X12 = 2;
 
 struct Desc3 {
     int n[3];                  // nx, ny, nz
@@ -58,8 +55,9 @@ struct Desc3 {
     int tailw12, tailp12, tailk12;  // packed tail (tailw12 > 0): the last nx mod 60 columns of
                                     // tailp12 planes per wavefront, lanes in segments of
                                     // tailw12 = that + 4; tailk12 plane groups
-    int strips64, segs3, planes3;   // x3 tiles: 64-column strips, z segments of planes3
-    int segs4, planes4;             // source tiles: z segments of planes4 (blocks of four rows)
+    int bx, by, ntx, nty;           // x3 and source tiles: bx x by threads, (bx - 2) x (by - 2)
+                                    // columns of output, ntx x nty tiles
+    int segs3, planes3;             // their z segments of planes3
     long long plane;           // elements per field = pitch * ny * nz
     int bc[6];
     int fixed_dt, max_retries;
@@ -251,26 +249,42 @@ __device__ __forceinline__ void march_push(const Q4<T>& q, const March4<T>& in, 
     out.lo[3] = tup[3];
 }
 
-// Fold a lane's CFL bookkeeping into the clock (one atomic per wavefront).
+// Wait for the loads of q here.  Loads and stores share one in-order counter,
+// and after stores under a condition the compiler can only wait for a load by
+// waiting for all but as many newer operations as are certain to have been
+// issued: for the loads two rows ahead as well, the whole latency on every row.
+// Placed ahead of a row's stores, the wait is for the next row's loads only.
 template <typename T>
-__device__ __forceinline__ void cfl_commit(const Desc3& d, const Cfl<T>& acc, bool counted)
+__device__ __forceinline__ void wait_loads(Q4<T>& q)
+{
+    asm volatile("" : "+v"(q.R), "+v"(q.n), "+v"(q.a), "+v"(q.b));
+}
+
+// Fold a block's CFL bookkeeping into the attempt's slot: over the wavefront,
+// then in LDS (sh: two words per wavefront) over the block.  Every thread of the
+// block calls it, after its last use of sh.
+template <typename T>
+__device__ __forceinline__ void cfl_commit(const Attempt& at, const Cfl<T>& acc, bool counted, T* sh)
 {
     T m;
     bool nh, nf;
     acc.finish(counted, m, nh, nf);
-    const int lane = threadIdx.x & (WAVE - 1);
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, waves = blockDim.x / WAVE;
     for (int off = 32; off >= 1; off >>= 1) m = max_(m, perm(m, lane ^ off));
     const bool anyh = __any(nh), anyf = __any(nf);
+    __syncthreads();
     if (lane == 0) {
-        atomicMax(&d.clk->smax_bits, (unsigned long long)__double_as_longlong(cfl_speed<T>(m)));
-        const unsigned fl = (anyh ? FLAG_NONHYP : 0u) | (anyf ? FLAG_NONFINITE : 0u);
-        if (fl) atomicOr(&d.clk->flags, fl);
+        sh[2 * wave] = m;
+        sh[2 * wave + 1] = (anyh ? T(1) : T(0)) + (anyf ? T(2) : T(0));
     }
-}
-
-__device__ __forceinline__ bool step_owed(const Clock* c, int force)
-{
-    return force || (c->status == 0 && c->accepted < c->target);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    int fl = 0;
+    for (int k = 0; k < waves; ++k) {
+        m = max_(m, sh[2 * k]);
+        fl |= (int)sh[2 * k + 1];
+    }
+    cfl_raise(at, cfl_speed<T>(m), (fl & 1) != 0, (fl & 2) != 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -320,7 +334,7 @@ __device__ __forceinline__ void sweep12_lanes(const Desc3& d, int tile, int& seg
 }
 
 template <typename T>
-__device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Clock* clk)
+__device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Attempt& at)
 {
     const int nx = d.n[0], ny = d.n[1];
     const int lane = threadIdx.x & (WAVE - 1);
@@ -328,11 +342,10 @@ __device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Clo
     bool lane_ok;
     sweep12_lanes(d, tile, seg, k, col, loc, w, lane_ok);
     const int r0 = seg * d.rows12, r1 = min(r0 + d.rows12, ny);
-    const T dt = (T)clk->dt;
-    const int cur = clk->cur;
-    const T* inR = (const T*)d.buf[buf_rho(cur)];
-    const T* inM = (const T*)d.buf[buf_mom(cur)];
-    T* out = (T*)d.buf[buf_x12(cur)];
+    const T dt = (T)at.dt;
+    const T* inR = (const T*)d.buf[buf_rho(at.cur)];
+    const T* inM = (const T*)d.buf[buf_mom(at.cur)];
+    T* out = (T*)d.buf[BUF_X12];
     const T beta = (T)d.beta;
     const bool perx = d.bc[0] == FVNA_BC_PERIODIC, pery = d.bc[2] == FVNA_BC_PERIODIC;
     bool xneg;
@@ -392,7 +405,7 @@ __device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Clo
     March4<T> A, B;
     march_zero(A);
     const int v0 = r0 - HALO12, v1 = r1 + HALO12;
-    auto step_row = [&](int v, const Q4<T>& raw, const March4<T>& mi, March4<T>& mo) {
+    auto step_row = [&](int v, const Q4<T>& raw, Q4<T>& next, const March4<T>& mi, March4<T>& mo) {
         bool yneg;
         (void)side_map(d, 1, v, yneg);
         const Q4<T> x = xsweep(raw);
@@ -404,6 +417,7 @@ __device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Clo
         const bool cnt = v > v0 && (pery || (v >= 0 && v <= ny));
         Q4<T> dn;
         march_push(q, mi, mo, beta, dt, cnt, yacc, dn);
+        wait_loads(next);
         const int j = v - 2;
         if (j >= r0 && out_lane) {
             T* o = out_l + (size_t)j * (size_t)d.pitch;
@@ -416,17 +430,18 @@ __device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Clo
     // two rows of loads in flight ahead of the row being swept (rows past
     // v1 - 1 are clamped by the side rule and never used)
     Q4<T> p0 = load_row(v0), p1 = load_row(v0 + 1);
+    wait_loads(p0);
     int v = v0;
 #pragma unroll 1
     for (; v + 1 < v1; v += 2) {
         Q4<T> r = p0;
         p0 = load_row(v + 2);
-        step_row(v, r, A, B);
+        step_row(v, r, p1, A, B);
         r = p1;
         p1 = load_row(v + 3);
-        step_row(v + 1, r, B, A);
+        step_row(v + 1, r, p0, B, A);
     }
-    if (v < v1) step_row(v, p0, A, B);
+    if (v < v1) step_row(v, p0, p1, A, B);
 
     // x1 interfaces: a lane's lies between columns col - 1 and col (the
     // first lane of a segment has no left neighbour); x2 interfaces: lanes
@@ -441,253 +456,161 @@ __device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Clo
     T m = max_(sx, sy);
     for (int off = 32; off >= 1; off >>= 1) m = max_(m, perm(m, lane ^ off));
     const bool anyh = __any(hx || hy), anyf = __any(fx || fy);
-    if (lane == 0) {
-        atomicMax(&d.clk->smax_bits, (unsigned long long)__double_as_longlong(cfl_speed<T>(m)));
-        const unsigned fl = (anyh ? FLAG_NONHYP : 0u) | (anyf ? FLAG_NONFINITE : 0u);
-        if (fl) atomicOr(&d.clk->flags, fl);
-    }
+    if (lane == 0) cfl_raise(at, cfl_speed<T>(m), anyh, anyf);
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Occupancy<T>::waves)))
-void k3_sweep12(Desc3 d, int force)
+void k3_sweep12(Desc3 d, int force, int pos, long long owed)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK + wave;
     const int nfull = d.strips12 * d.segs12 * d.n[2];
     if (tile >= nfull + d.tailk12 * d.segs12) return;
-    const Clock* clk = d.clk;
-    if (!step_owed(clk, force)) return;
-    sweep12_tile<T>(d, tile, clk);
+    pos = max(pos, 0);
+    Attempt at;
+    if (step_begin(d, force, pos, owed, at)) sweep12_tile<T>(d, tile, at);
+    if (tile == 0 && (threadIdx.x & (WAVE - 1)) == 0) step_end(d, pos, owed);
 }
 
 // ---------------------------------------------------------------------------
-// x3 sweep: lane = column strip * 64 + lane, row j, planes k0 .. k1 - 1 of
-// the output; planes k0 - 2 .. k1 + 1 are pushed through the march, those
-// outside the grid by the x3 side rule applied to the x2-swept state.
+// x3 sweep and source (3-D form of eq. fs:source, forward Euler: M_c += dt
+// delta~ lap(u_c), 7-point Laplacian of u_c = M_c / (1 + R)) in one pass.
+//
+// A block takes a tile of bx x by columns (thread t: row t / bx, column t mod
+// bx, the outermost ones halo) and a segment of planes k0 .. k1 - 1.  Every
+// thread marches its column through the x3 sweep in registers; planes k0 - 3 ..
+// k1 + 2 are pushed (outside the grid by the x3 side rule applied to the
+// x2-swept state), which completes planes k0 - 1 .. k1.  A completed plane's
+// velocities go to LDS, and one plane later, when the plane above is known
+// too, each thread finds its x1 and x2 neighbours there: the halo threads hold
+// the neighbour columns, or by the side rule the ghosts (mirrored normal
+// velocity).  Two LDS planes and one barrier per plane: neighbours are read
+// before the barrier of the iteration that publishes the next plane.
+//
+// The two separate kernels this replaces moved the state over HBM twice
+// (256^3, one step: x3 sweep 129 us and source 124 us FP32, both at 4.3 TB/s,
+// 206 and 239 us FP64); here the swept state never leaves the CU, at the price
+// of marching the halo columns (15 to 25% of the threads) and two more planes
+// per segment.
 // ---------------------------------------------------------------------------
+template <typename T> struct Vel { T u1, u2, u3; };
+
+// Threads of a block: FP32 four wavefronts per SIMD, FP64 two.
+template <typename T> struct Sweep3 { static constexpr int threads = sizeof(T) == 8 ? 512 : 1024; };
+
 template <typename T>
-__global__ __launch_bounds__(256) void k3_sweep3(Desc3 d, int force)
+__global__ __launch_bounds__(Sweep3<T>::threads) void k3_sweep3s(Desc3 d, int force, int pos, long long owed)
 {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK + wave;
-    const int ntiles = d.strips64 * d.n[1] * d.segs3;
-    if (tile >= ntiles) return;
-    const Clock* clk = d.clk;
-    if (!step_owed(clk, force)) return;
-    const int strip = tile % d.strips64;
-    const int j = (tile / d.strips64) % d.n[1];
-    const int seg = tile / (d.strips64 * d.n[1]);
+    constexpr int N = Sweep3<T>::threads;
+    __shared__ T ys[2][3][N];                          // [plane parity][component][thread]
+    Attempt at;
+    // the whole block: the same words
+    if (!step_again(d, force, max(pos, 0), owed, at)) return;
+    const int b = xcd_block(blockIdx.x, gridDim.x);
+    const int tx = b % d.ntx, ty = (b / d.ntx) % d.nty, seg = b / (d.ntx * d.nty);
     const int nx = d.n[0], ny = d.n[1], nz = d.n[2];
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int col = strip * WAVE + lane;
-    const int scol = min(col, nx - 1);
+    const int t = threadIdx.x, bx = d.bx, by = d.by;
+    const int row = t / bx, cx = t - row * bx;
+    const int gx = tx * (bx - 2) - 1 + cx, gy = ty * (by - 2) - 1 + row;
+    bool xneg, yneg;
+    const int sx = side_map(d, 0, gx, xneg), sy = side_map(d, 1, gy, yneg);
+    const bool real = row < by && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
+    const bool out = real && cx >= 1 && cx < bx - 1 && row >= 1 && row < by - 1;
     const int k0 = seg * d.planes3, k1 = min(k0 + d.planes3, nz);
-    const T dt = (T)clk->dt;
-    const int cur = clk->cur;
-    const T* in = (const T*)d.buf[buf_x12(cur)];
-    T* outR = (T*)d.buf[buf_mom(cur)];          // density plane of the momentum buffer
-    T* outM = (T*)d.buf[buf_rho(cur)];          // momentum planes of the density buffer
-    const T beta = (T)d.beta;
+    const T dt = (T)at.dt, beta = (T)d.beta;
+    const T kd = dt * (T)d.delta;
     const bool perz = d.bc[4] == FVNA_BC_PERIODIC;
     const size_t pl = (size_t)d.plane;
     const size_t zstride = (size_t)ny * (size_t)d.pitch;
-    const size_t rowoff = (size_t)j * (size_t)d.pitch + (size_t)scol;
+    const T* __restrict__ in = (const T*)d.buf[BUF_X12];
+    T* __restrict__ outR = (T*)d.buf[buf_rho(at.cur ^ 1)];
+    T* __restrict__ outM = (T*)d.buf[buf_mom(at.cur ^ 1)];
+    const unsigned cell = (unsigned)sy * (unsigned)d.pitch + (unsigned)sx;      // within a plane
     Cfl<T> acc;
     March4<T> A, B;
     march_zero(A);
-    const int v0 = k0 - 2, v1 = k1 + 2;
-    // raw x2-swept cell of the plane that plane v stands for, split-local
-    // for x3 (normal = M3), the mirror applied
+    const int v0 = k0 - 3, v1 = k1 + 3;
+    // raw x2-swept cell of the plane that plane v stands for, split-local for
+    // x3 (normal = M3), the mirror applied
     auto load_plane = [&](int v) -> Q4<T> {
         bool zneg;
-        const int sk = side_map(d, 2, v, zneg);
-        const size_t o = (size_t)sk * zstride + rowoff;
-        Q4<T> q{in[o], in[3 * pl + o], in[pl + o], in[2 * pl + o]};
+        const T* p = in + (size_t)side_map(d, 2, v, zneg) * zstride;
+        Q4<T> q{p[cell], (p + 3 * pl)[cell], (p + pl)[cell], (p + 2 * pl)[cell]};
         if (zneg) q.n = -q.n;
         return q;
     };
-    auto step_plane = [&](int v, const Q4<T>& q, const March4<T>& mi, March4<T>& mo) {
-        const bool cnt = v > v0 && (perz || (v >= 0 && v <= nz));
+    Vel<T> ub{T(0), T(0), T(0)}, uc{T(0), T(0), T(0)};
+    Vel<T> mc{T(0), T(0), T(0)};                       // momenta of the plane awaiting its source
+    auto step_plane = [&](int v, const Q4<T>& q, Q4<T>& next, const March4<T>& mi, March4<T>& mo) {
         Q4<T> dn;
-        march_push(q, mi, mo, beta, dt, cnt, acc, dn);
-        const int kk = v - 2;
-        if (kk >= k0 && col < nx) {
-            const size_t w = (size_t)kk * zstride + (size_t)j * (size_t)d.pitch + (size_t)col;
-            outR[w] = dn.R;
-            outM[pl + w] = dn.a;
-            outM[2 * pl + w] = dn.b;
-            outM[3 * pl + w] = dn.n;
+        march_push(q, mi, mo, beta, dt, v > v0 && (perz || (v >= 0 && v <= nz)), acc, dn);
+        const int m = v - 2, j = v - 3;                // completed plane, plane taking its source
+        const T ir = rcp(T(1) + dn.R);
+        const Vel<T> ua{dn.a * ir, dn.b * ir, dn.n * ir};
+        Vel<T> xl, xh, yl, yh;
+        const bool src = out && j >= k0;               // j < k1 always
+        if (src) {
+            const T (*s)[N] = ys[j & 1];
+            xl = Vel<T>{s[0][t - 1], s[1][t - 1], s[2][t - 1]};
+            xh = Vel<T>{s[0][t + 1], s[1][t + 1], s[2][t + 1]};
+            yl = Vel<T>{s[0][t - bx], s[1][t - bx], s[2][t - bx]};
+            yh = Vel<T>{s[0][t + bx], s[1][t + bx], s[2][t + bx]};
         }
+        // a halo thread's cell stands in for the ghost beside its neighbour
+        T (*w)[N] = ys[m & 1];
+        w[0][t] = xneg ? -ua.u1 : ua.u1;
+        w[1][t] = yneg ? -ua.u2 : ua.u2;
+        w[2][t] = ua.u3;
+        wait_loads(next);
+        if (src) {
+            Vel<T> zl = ub, zh = ua;
+            if (!perz && j == 0) {
+                zl = uc;
+                if (d.bc[4] == FVNA_BC_REFLECT) zl.u3 = -zl.u3;
+            }
+            if (!perz && j == nz - 1) {
+                zh = uc;
+                if (d.bc[5] == FVNA_BC_REFLECT) zh.u3 = -zh.u3;
+            }
+            // the oracle's order: -6 u_c, then x-, x+, y-, y+, z-, z+
+            auto lap = [&](T c, T a0, T a1, T a2, T a3, T a4, T a5) {
+                return ((((((T(-6) * c + a0) + a1) + a2) + a3) + a4) + a5);
+            };
+            const T l1 = lap(uc.u1, xl.u1, xh.u1, yl.u1, yh.u1, zl.u1, zh.u1);
+            const T l2 = lap(uc.u2, xl.u2, xh.u2, yl.u2, yh.u2, zl.u2, zh.u2);
+            const T l3 = lap(uc.u3, xl.u3, xh.u3, yl.u3, yh.u3, zl.u3, zh.u3);
+            T* o = outM + (size_t)j * zstride;
+            (o + pl)[cell] = fma_(kd, l1, mc.u1);
+            (o + 2 * pl)[cell] = fma_(kd, l2, mc.u2);
+            (o + 3 * pl)[cell] = fma_(kd, l3, mc.u3);
+        }
+        if (out && m >= k0 && m < k1) (outR + (size_t)m * zstride)[cell] = dn.R;
+        mc = Vel<T>{dn.a, dn.b, dn.n};
+        ub = uc;
+        uc = ua;
+        __syncthreads();
     };
+    // two planes of loads in flight ahead of the one being pushed
     Q4<T> p0 = load_plane(v0), p1 = load_plane(v0 + 1);
+    wait_loads(p0);
     int v = v0;
 #pragma unroll 1
     for (; v + 1 < v1; v += 2) {
         Q4<T> r = p0;
         p0 = load_plane(v + 2);
-        step_plane(v, r, A, B);
+        step_plane(v, r, p1, A, B);
         r = p1;
         p1 = load_plane(v + 3);
-        step_plane(v + 1, r, B, A);
+        step_plane(v + 1, r, p0, B, A);
     }
-    if (v < v1) step_plane(v, p0, A, B);
-    cfl_commit(d, acc, col < nx);
+    if (v < v1) step_plane(v, p0, p1, A, B);
+    cfl_commit(at, acc, real, &ys[0][0][0]);
 }
 
-// ---------------------------------------------------------------------------
-// Source (3-D form of eq. fs:source, forward Euler): M_c += dt delta~ lap(u_c),
-// 7-point Laplacian of u_c = M_c / (1 + R); the density is not rewritten (it
-// stays where the x3 sweep put it).  A block of
-// SRC_ROWS (= s) wavefronts takes rows s g .. s g + s - 1 of one 64-column
-// strip over planes k0 .. k1 - 1: lane = column, wave = row.  Per plane each
-// wave publishes its row's velocities in LDS (the first and last waves also
-// the rows s g - 1 and s g + s),
-// and after one barrier reads its x2 neighbours there; x3 neighbours are
-// carried in registers, x1 neighbours come over DPP (the strip's end lanes
-// load theirs).  Neighbours outside the grid follow the side rules (mirrored
-// normal velocity); rows past ny are such ghost rows and are never stored.
-// Every wave of a block runs the same number of barriers: the only early
-// exits come before the loop and hold for the whole block.
-// ---------------------------------------------------------------------------
-template <typename T> struct Vel { T u1, u2, u3; };
-
-// Rows (wavefronts) per source block.  Eight rows read fewer halo rows (10
-// per 8 instead of 6 per 4) but measured level: 256^3 per step FP32 0.451 ms
-// with 4 or 8, FP64 0.783 / 0.775 ms.
-#ifndef FVNA3_SRC_ROWS
-#define FVNA3_SRC_ROWS 4
-#endif
-constexpr int SRC_ROWS = FVNA3_SRC_ROWS;
-
-template <typename T>
-__global__ __launch_bounds__(WAVE * SRC_ROWS) void k3_source(Desc3 d, int force)
+__global__ void k3_ctrl_fold(Desc3 d, int last, long long owed)
 {
-    // [plane parity][row g SRC_ROWS - 1 .. (g + 1) SRC_ROWS][component][lane]
-    __shared__ T ys[2][SRC_ROWS + 2][3][WAVE];
-    const int ngroups = (d.n[1] + SRC_ROWS - 1) / SRC_ROWS;
-    const int b = xcd_block(blockIdx.x, gridDim.x);
-    if (b >= d.strips64 * ngroups * d.segs4) return;        // the whole block
-    const Clock* clk = d.clk;
-    if (!step_owed(clk, force)) return;                       // the whole block (same clock)
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int strip = b % d.strips64;
-    const int g = (b / d.strips64) % ngroups;
-    const int seg = b / (d.strips64 * ngroups);
-    const int nx = d.n[0], ny = d.n[1], nz = d.n[2];
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int col = strip * WAVE + lane;
-    const int j = SRC_ROWS * g + wave;
-    // lanes past the last column hold the x+ ghost by the side rule (the
-    // lane after the last column is that column's right neighbour); rows past
-    // the last row likewise hold the y+ ghost
-    bool oneg, jneg;
-    const int scol = side_map(d, 0, col, oneg);
-    const int sj = side_map(d, 1, j, jneg);
-    const int k0 = seg * d.planes4, k1 = min(k0 + d.planes4, nz);
-    const T dt = (T)clk->dt;
-    const int cur = clk->cur;
-    const T* inR = (const T*)d.buf[buf_mom(cur)];     // the x3 sweep's density ...
-    const T* inM = (const T*)d.buf[buf_rho(cur)];     // ... and momenta
-    T* out = (T*)d.buf[buf_x12(cur)];                 // momenta only
-    const T kd = dt * (T)d.delta;
-    const size_t pl = (size_t)d.plane;
-    const size_t zstride = (size_t)ny * (size_t)d.pitch;
-    const bool edge = lane == 0 || lane == WAVE - 1;
-    bool eneg = false;
-    int ecol = scol;
-    if (lane == 0) ecol = side_map(d, 0, col - 1, eneg);
-    else if (lane == WAVE - 1) ecol = side_map(d, 0, col + 1, eneg);
-    // halo rows: wave 0 publishes row 4g - 1, wave 3 row 4g + 4
-    const bool halo = wave == 0 || wave == SRC_ROWS - 1;
-    bool hneg = false;
-    const int hj = halo ? side_map(d, 1, wave == 0 ? SRC_ROWS * g - 1 : SRC_ROWS * (g + 1), hneg) : sj;
-    const int hslot = wave == 0 ? 0 : SRC_ROWS + 1;
-    // raw cell at element offset o with the mirrored components negated
-    auto raw = [&](size_t o, bool neg1, bool neg2, bool neg3) -> Q4<T> {
-        Q4<T> q{inR[o], inM[pl + o], inM[2 * pl + o], inM[3 * pl + o]};
-        if (neg1) q.n = -q.n;
-        if (neg2) q.a = -q.a;
-        if (neg3) q.b = -q.b;
-        return q;
-    };
-    auto vel = [&](const Q4<T>& q) -> Vel<T> {
-        const T ir = rcp(T(1) + q.R);
-        return Vel<T>{q.n * ir, q.a * ir, q.b * ir};
-    };
-    // this lane's cell in plane v (side rule along x3)
-    auto own = [&](int v) -> Q4<T> {
-        bool zneg;
-        const int sk = side_map(d, 2, v, zneg);
-        return raw((size_t)sk * zstride + (size_t)sj * (size_t)d.pitch + (size_t)scol, oneg, jneg, zneg);
-    };
-    // the halo row (waves 0, 3) and the end lanes' x neighbours in plane v
-    // (v inside the grid when used; clamped otherwise)
-    const Q4<T> zero{T(0), T(0), T(0), T(0)};
-    auto side_cells = [&](int v, Q4<T>& h, Q4<T>& e) {
-        const size_t zo = (size_t)min(max(v, 0), nz - 1) * zstride;
-        h = zero;
-        e = zero;
-        if (halo) h = raw(zo + (size_t)hj * (size_t)d.pitch + (size_t)scol, oneg, hneg, false);
-        if (edge) e = raw(zo + (size_t)sj * (size_t)d.pitch + (size_t)ecol, eneg, jneg, false);
-    };
-    // loads run ahead: this lane's cells two planes, the side cells one plane
-    Q4<T> q0 = own(k0), q1 = own(k0 + 1), hq, eq;
-    side_cells(k0, hq, eq);
-    Vel<T> ub = vel(own(k0 - 1)), uc = vel(q0);
-#pragma unroll 1
-    for (int k = k0; k < k1; ++k) {
-        const Q4<T> q2 = own(k + 2);
-        Q4<T> hq1, eq1;
-        side_cells(k + 1, hq1, eq1);
-        const Vel<T> ua = vel(q1);
-        // publish plane k's velocities of this wave's row (and the halo row)
-        T (*slot)[3][WAVE] = ys[k & 1];
-        slot[wave + 1][0][lane] = uc.u1;
-        slot[wave + 1][1][lane] = uc.u2;
-        slot[wave + 1][2][lane] = uc.u3;
-        if (halo) {
-            const Vel<T> hv = vel(hq);
-            slot[hslot][0][lane] = hv.u1;
-            slot[hslot][1][lane] = hv.u2;
-            slot[hslot][2][lane] = hv.u3;
-        }
-        // every wave has published plane k; the slot written next (plane
-        // k + 1) was last read before the previous barrier
-        __syncthreads();
-        const Vel<T> yl{slot[wave][0][lane], slot[wave][1][lane], slot[wave][2][lane]};
-        const Vel<T> yh{slot[wave + 2][0][lane], slot[wave + 2][1][lane], slot[wave + 2][2][lane]};
-        const Vel<T> e = vel(eq);
-        Vel<T> xl, xh;
-        xl.u1 = from_lo(uc.u1); xl.u2 = from_lo(uc.u2); xl.u3 = from_lo(uc.u3);
-        xh.u1 = from_hi(uc.u1); xh.u2 = from_hi(uc.u2); xh.u3 = from_hi(uc.u3);
-        if (lane == 0) xl = e;
-        if (lane == WAVE - 1) xh = e;
-        // the oracle's order: -6 u_c, then x-, x+, y-, y+, z-, z+
-        auto lap = [&](T c, T a0, T a1, T a2, T a3, T a4, T a5) {
-            return ((((((T(-6) * c + a0) + a1) + a2) + a3) + a4) + a5);
-        };
-        const T l1 = lap(uc.u1, xl.u1, xh.u1, yl.u1, yh.u1, ub.u1, ua.u1);
-        const T l2 = lap(uc.u2, xl.u2, xh.u2, yl.u2, yh.u2, ub.u2, ua.u2);
-        const T l3 = lap(uc.u3, xl.u3, xh.u3, yl.u3, yh.u3, ub.u3, ua.u3);
-        if (col < nx && j < ny) {
-            const size_t o = (size_t)k * zstride + (size_t)j * (size_t)d.pitch + (size_t)col;
-            out[pl + o] = fma_(kd, l1, q0.n);
-            out[2 * pl + o] = fma_(kd, l2, q0.a);
-            out[3 * pl + o] = fma_(kd, l3, q0.b);
-        }
-        ub = uc;
-        uc = ua;
-        q0 = q1;
-        q1 = q2;
-        hq = hq1;
-        eq = eq1;
-    }
-}
-
-__global__ void k3_ctrl(Desc3 d)
-{
-    if (threadIdx.x == 0) control_attempt(d.clk, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 3);
+    if (threadIdx.x == 0) *d.clk = fold_decision(d, last, owed);
 }
 
 __global__ void k3_bump(Clock* c, long long n)
@@ -792,8 +715,9 @@ fvna_status validate3(const fvna3_params* p)
     return FVNA_OK;
 }
 
-// scratch layout: [Clock][staging of one field]
-constexpr size_t OFF3_STAGE = 256;
+// scratch layout: [Clock, ClockAux][staging of one field]
+constexpr size_t OFF3_STAGE = 768;
+static_assert(CLOCK_AUX_OFFSET + sizeof(ClockAux) <= OFF3_STAGE, "clock and shadow states before the staging area");
 
 int cu_count3()
 {
@@ -803,15 +727,30 @@ int cu_count3()
     return n;
 }
 
-// Segment lengths: enough tiles to fill every wavefront slot of the device
-// once (CUs x 4 SIMDs x `waves`) where the grid allows, never shorter than 16
-// cells (the two warm-up cells at each end are repeated work).
-int seg_len(long long tiles_per_seg_unit, int n, int cus, int waves)
+// Tiles of k3_sweep3s: the width bx, with by = threads / bx rows, and the
+// number of z segments of least cost, counted in planes pushed one after
+// another: rounds of one block per CU, times planes per segment + 6.
+void plan_sweep3(Desc3& d, int threads, int cus)
 {
-    const long long slots = (long long)cus * 4 * waves;
-    const long long per = std::max(1ll, slots / std::max(1ll, tiles_per_seg_unit));
-    const long long len = (n + per - 1) / per;
-    return (int)std::max(16ll, std::min(len, (long long)n));
+    double best = 1e30;
+    const int nz = d.n[2];
+    for (int bx = 8; bx <= std::min(threads / 4, d.n[0] + 2); ++bx) {
+        const int by = std::min(threads / bx, d.n[1] + 2);
+        const long long ntx = (d.n[0] + bx - 3) / (bx - 2), nty = (d.n[1] + by - 3) / (by - 2), xy = ntx * nty;
+        for (int segs = 1; segs <= nz; ++segs) {
+            const int planes = (nz + segs - 1) / segs;
+            const long long blocks = xy * ((nz + planes - 1) / planes);
+            // rows of a tile shorter than a 128-byte line waste part of what they fetch
+            const double cost = (double)((blocks + cus - 1) / cus) * (planes + 6) * (1.0 + 1.0 / bx);
+            if (cost < best) {
+                best = cost;
+                d.bx = bx; d.by = by; d.ntx = (int)ntx; d.nty = (int)nty;
+                d.planes3 = planes;
+                d.segs3 = (nz + planes - 1) / planes;
+            }
+            if (planes <= 2 || blocks > 64ll * cus) break;
+        }
+    }
 }
 
 }  // namespace
@@ -824,27 +763,27 @@ struct fvna3_ctx {
     char* scratch;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    void (*launch)(const Desc3&, int force, hipStream_t) = nullptr;
+    void (*attempt)(const Desc3&, int force, int pos, long long owed, hipStream_t) = nullptr;
 };
 
 namespace {
 
 template <typename T>
-void launch_sweeps(const Desc3& d, int force, hipStream_t s, bool source)
+void launch_attempt(const Desc3& d, int force, int pos, long long owed, hipStream_t s)
 {
     const int t12 = (d.strips12 * d.n[2] + d.tailk12) * d.segs12;
-    const int t3 = d.strips64 * d.n[1] * d.segs3;
-    hipLaunchKernelGGL(k3_sweep12<T>, dim3((t12 + 3) / 4), dim3(256), 0, s, d, force);
-    hipLaunchKernelGGL(k3_sweep3<T>, dim3((t3 + 3) / 4), dim3(256), 0, s, d, force);
-    const int tsrc = d.strips64 * ((d.n[1] + SRC_ROWS - 1) / SRC_ROWS) * d.segs4;    // blocks of SRC_ROWS rows
-    if (source) hipLaunchKernelGGL(k3_source<T>, dim3(tsrc), dim3(WAVE * SRC_ROWS), 0, s, d, force);
+    hipLaunchKernelGGL(k3_sweep12<T>, dim3((t12 + 3) / 4), dim3(256), 0, s, d, force, pos, owed);
+    hipLaunchKernelGGL(k3_sweep3s<T>, dim3(d.ntx * d.nty * d.segs3), dim3(Sweep3<T>::threads), 0, s, d, force, pos,
+                       owed);
 }
 
-template <typename T>
-void launch_attempt(const Desc3& d, int force, hipStream_t s)
+// n attempts in a row and the closing decision (as launch_attempts in two
+// dimensions).
+void launch_attempts3(fvna3_ctx* c, int n, long long owed, hipStream_t s)
 {
-    launch_sweeps<T>(d, force, s, true);
-    hipLaunchKernelGGL(k3_ctrl, dim3(1), dim3(64), 0, s, d);
+    if (n <= 0) return;
+    for (int k = 0; k < n; ++k) c->attempt(c->d, 0, k, owed, s);
+    hipLaunchKernelGGL(k3_ctrl_fold, dim3(1), dim3(64), 0, s, c->d, n - 1, owed);
 }
 
 void drop_graph3(fvna3_ctx* c)
@@ -860,7 +799,7 @@ fvna_status build_graph3(fvna3_ctx* c)
 {
     if (c->exec) return FVNA_OK;
     HIP3(hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < GRAPH3_CHUNK; ++k) c->launch(c->d, 0, c->cap);
+    launch_attempts3(c, GRAPH3_CHUNK, 0, c->cap);
     hipGraph_t g = nullptr;
     HIP3(hipStreamEndCapture(c->cap, &g));
     c->graph = g;
@@ -868,12 +807,14 @@ fvna_status build_graph3(fvna3_ctx* c)
     return FVNA_OK;
 }
 
-fvna_status enqueue3(fvna3_ctx* c, long long attempts)
+fvna_status enqueue3(fvna3_ctx* c, long long attempts, long long owed = 0)
 {
-    fvna_status s = build_graph3(c);
-    if (s) return s;
-    for (long long k = 0; k < attempts / GRAPH3_CHUNK; ++k) HIP3(hipGraphLaunch(c->exec, c->s));
-    for (long long k = 0; k < attempts % GRAPH3_CHUNK; ++k) c->launch(c->d, 0, c->s);
+    if (attempts >= GRAPH3_CHUNK) {
+        const fvna_status s = build_graph3(c);
+        if (s) return s;
+        for (long long k = 0; k < attempts / GRAPH3_CHUNK; ++k) HIP3(hipGraphLaunch(c->exec, c->s));
+    }
+    launch_attempts3(c, (int)(attempts % GRAPH3_CHUNK), owed, c->s);
     HIP3(hipGetLastError());
     return FVNA_OK;
 }
@@ -945,11 +886,6 @@ fvna_status fvna3_create(const fvna3_params* p, void* buf_a, void* buf_b, void* 
     d.pitch = pitch3(p);
     d.plane = (long long)d.pitch * p->ny * p->nz;
     const int cus = cu_count3();
-    // resident waves per SIMD the kernels' registers allow: FP32 5-6, FP64 3-4
-#ifndef FVNA3_WAVES
-#define FVNA3_WAVES 4
-#endif
-    const int waves = p->precision == FVNA_F64 ? 2 : FVNA3_WAVES;
     // x1-x2 tiles: full 60-column strips, and the remaining nx mod 60
     // columns packed several planes to a wavefront when at least two fit
     // (256^3 FP32: 3330 wavefronts instead of 3840)
@@ -971,26 +907,28 @@ fvna_status fvna3_create(const fvna3_params* p, void* buf_a, void* buf_b, void* 
     // row segments for about six x1-x2 tiles per SIMD: several rounds of
     // wavefronts let the dispatcher even out the load of the SIMDs, where
     // one round leaves some with a wavefront more than others (256^3, per
-    // step: FP32 0.470 ms with one round of 86-row tiles, 0.448 with 43-row
-    // tiles; FP64 0.918 with whole 256-row columns, 0.762 with 43 rows;
-    // 64 / 52 / 37 rows measured 0.459 / 0.453 / 0.450 and 0.769 / 0.773 /
-    // 0.764 ms); never fewer than 16 rows (two warm-up rows at each end)
+    // step: FP32 325 us with 43-row tiles, 333 with 64, 345 with 86, 371 with
+    // 128; 332 with 25).  A grid too small for that at 16 rows takes the rows
+    // of least (rows + 4 warm-up rows) x (1 with one wavefront per SIMD, 1.6
+    // with two, in proportion beyond), at least 4 (64^3 FP32: 6 rows 32.2 us per
+    // step, 16 rows 39.5, 4 rows 43.4; 90 x 75 x 64 FP64: 10 rows 42.0, 16 46.7).
     {
         const long long units = (long long)d.strips12 * p->nz + d.tailk12;
-        const long long want = 6ll * cus * 4;
+        const long long simds = 4ll * cus, want = 6 * simds;
         const long long nseg = std::max(1ll, (want + units - 1) / units);
-        d.rows12 = (int)std::max(16ll, std::min((long long)p->ny, ((long long)p->ny + nseg - 1) / nseg));
-        d.rows12 = std::min(d.rows12, p->ny);
+        long long rows = (p->ny + nseg - 1) / nseg;
+        if (rows < 16) {
+            double best = 1e30;
+            for (long long r = std::min(4, p->ny); r <= p->ny; ++r) {
+                const double w = (double)(units * ((p->ny + r - 1) / r)) / (double)simds;
+                const double cost = (double)(r + 2 * HALO12) * (w <= 1.0 ? 1.0 : w <= 2.0 ? 1.6 : 0.8 * w);
+                if (cost < best) { best = cost; rows = r; }
+            }
+        }
+        d.rows12 = (int)std::min(rows, (long long)p->ny);
     }
     d.segs12 = (p->ny + d.rows12 - 1) / d.rows12;
-    d.strips64 = (p->nx + WAVE - 1) / WAVE;
-    d.planes3 = seg_len((long long)d.strips64 * p->ny, p->nz, cus, waves);
-    d.segs3 = (p->nz + d.planes3 - 1) / d.planes3;
-    // the source kernel's blocks hold one plane's rows in LDS and are light:
-    // half the x3 sweep's z-segments, twice its waves (256^3 FP32: source
-    // blocks over 64 / 32 / 16 planes 0.486 / 0.469 / 0.473 ms per step)
-    d.planes4 = std::max(8, (d.planes3 + 1) / 2);
-    d.segs4 = (p->nz + d.planes4 - 1) / d.planes4;
+    plan_sweep3(d, p->precision == FVNA_F64 ? Sweep3<double>::threads : Sweep3<float>::threads, cus);
     for (int k = 0; k < 6; ++k) d.bc[k] = p->bc[k];
     d.fixed_dt = p->fixed_dt ? 1 : 0;
     d.max_retries = p->max_retries;
@@ -1002,7 +940,7 @@ fvna_status fvna3_create(const fvna3_params* p, void* buf_a, void* buf_b, void* 
     d.clk = (Clock*)scratch;
     c->scratch = (char*)scratch;
     c->s = (hipStream_t)stream;
-    c->launch = p->precision == FVNA_F64 ? launch_attempt<double> : launch_attempt<float>;
+    c->attempt = p->precision == FVNA_F64 ? launch_attempt<double> : launch_attempt<float>;
     if (hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking) != hipSuccess) {
         delete c;
         return fail3(FVNA_E_HIP, "cannot create the capture stream");
@@ -1046,9 +984,8 @@ fvna_status fvna3_set_state(fvna3_ctx* c, const double* rho_p, const double* m1,
     hipLaunchKernelGGL(k3_clock, dim3(1), dim3(64), 0, c->s, d.clk, 0.0, dt0, 0);
     HIP3(hipGetLastError());
     if (!(dt0 > 0)) {
-        // dt = 0: the x1, x2 and x3 sweeps see Q^0 (the source is not needed)
-        if (p.precision == FVNA_F64) launch_sweeps<double>(d, 1, c->s, false);
-        else launch_sweeps<float>(d, 1, c->s, false);
+        // dt = 0: the x1, x2 and x3 sweeps see Q^0 and the source adds nothing
+        c->attempt(d, 1, 0, 0, c->s);
         hipLaunchKernelGGL(k3_dt0, dim3(1), dim3(64), 0, c->s, d);
         HIP3(hipGetLastError());
     }
@@ -1065,9 +1002,10 @@ fvna_status fvna3_step(fvna3_ctx* c, int64_t nsteps)
     if (!c) return fail3(FVNA_E_INVALID, "ctx is NULL");
     if (nsteps < 0) return fail3(FVNA_E_INVALID, "nsteps must be >= 0");
     if (nsteps == 0) return FVNA_OK;
-    hipLaunchKernelGGL(k3_bump, dim3(1), dim3(64), 0, c->s, c->d.clk, (long long)nsteps);
+    const bool graph = nsteps >= GRAPH3_CHUNK;         // shorter runs carry their step count themselves
+    if (graph) hipLaunchKernelGGL(k3_bump, dim3(1), dim3(64), 0, c->s, c->d.clk, (long long)nsteps);
     HIP3(hipGetLastError());
-    fvna_status s = enqueue3(c, nsteps);
+    fvna_status s = enqueue3(c, nsteps, graph ? 0 : nsteps);
     if (s) return s;
     return sync3(c);
 }
@@ -1119,13 +1057,12 @@ fvna_status fvna3_time_step_kernels(fvna3_ctx* c, int32_t reps, double* ms)
     // back-to-back recomputations of the attempt the next step would make
     // (forced, no controller): the state and the clock are unchanged apart
     // from the attempt's speed maximum, which the next controller run clears
-    auto sweeps = c->p.precision == FVNA_F64 ? launch_sweeps<double> : launch_sweeps<float>;
     hipEvent_t e0, e1;
     HIP3(hipEventCreate(&e0));
     HIP3(hipEventCreate(&e1));
-    sweeps(c->d, 1, c->s, true);
+    c->attempt(c->d, 1, 0, 0, c->s);
     HIP3(hipEventRecord(e0, c->s));
-    for (int r = 0; r < reps; ++r) sweeps(c->d, 1, c->s, true);
+    for (int r = 0; r < reps; ++r) c->attempt(c->d, 1, 0, 0, c->s);
     HIP3(hipGetLastError());
     HIP3(hipEventRecord(e1, c->s));
     HIP3(hipEventSynchronize(e1));

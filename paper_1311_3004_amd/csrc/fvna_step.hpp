@@ -81,13 +81,33 @@ __device__ __forceinline__ Clock step_clock(const D& d, int pos, long long owed)
     unsigned long long* psb;
     unsigned int* pfl;
     cfl_slot(clk, (pos - 1) % 3, psb, pfl);
-    return control_next(h, *(ConstU64)psb, *(ConstU32)pfl, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 2);
+    const unsigned long long sb = *(ConstU64)psb;
+    const unsigned fl = *(ConstU32)pfl;
+    // every word the decision branches on is here before its first branch: one
+    // round trip to memory instead of one per branch
+    asm volatile("" ::"s"(sb), "s"(fl), "s"(h.accepted), "s"(h.target), "s"(h.status), "s"(h.retries), "s"(h.cur),
+                 "s"(h.dt), "s"(h.t), "s"(h.x_off));
+    return control_next(h, sb, fl, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 2);
 }
 
 template <typename D>
 __device__ __forceinline__ bool step_begin(const D& d, int force, int pos, long long owed, Attempt& at)
 {
     const Clock h = step_clock(d, pos, owed);
+    unsigned long long* sb;
+    unsigned int* fl;
+    cfl_slot(d.clk, pos % 3, sb, fl);
+    at = attempt_of(h, sb, fl);
+    return force || (h.status == 0 && h.accepted < h.target);
+}
+
+// For the further kernels of an attempt: the state its first kernel (which ran
+// step_begin and, in its step_end, stored the decision) ran with.
+template <typename D>
+__device__ __forceinline__ bool step_again(const D& d, int force, int pos, long long owed, Attempt& at)
+{
+    Clock h = read_clock(pos == 0 ? d.clk : &clock_aux(d.clk)->shadow[pos & 1]);
+    if (pos == 0) h.target += owed;
     unsigned long long* sb;
     unsigned int* fl;
     cfl_slot(d.clk, pos % 3, sb, fl);
