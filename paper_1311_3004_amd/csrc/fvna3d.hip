@@ -734,7 +734,7 @@ void plan_sweep3(Desc3& d, int threads, int cus)
 {
     double best = 1e30;
     const int nz = d.n[2];
-    for (int bx = 8; bx <= std::min(threads / 4, d.n[0] + 2); ++bx) {
+    for (int bx = std::min(8, d.n[0] + 2); bx <= std::min(threads / 4, d.n[0] + 2); ++bx) {
         const int by = std::min(threads / bx, d.n[1] + 2);
         const long long ntx = (d.n[0] + bx - 3) / (bx - 2), nty = (d.n[1] + by - 3) / (by - 2), xy = ntx * nty;
         for (int segs = 1; segs <= nz; ++segs) {
@@ -748,7 +748,7 @@ void plan_sweep3(Desc3& d, int threads, int cus)
                 d.planes3 = planes;
                 d.segs3 = (nz + planes - 1) / planes;
             }
-            if (planes <= 2 || blocks > 64ll * cus) break;
+            if (planes <= 2 || blocks > 16ll * cus) break;
         }
     }
 }
