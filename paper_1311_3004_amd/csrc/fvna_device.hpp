@@ -52,8 +52,8 @@ enum { FLAG_NONHYP = 1u, FLAG_NONFINITE = 2u };
 enum { ST_OK = 0, ST_NONHYP = 4, ST_NONFINITE = 5, ST_RETRIES = 6 };
 
 // Device-resident clock and control word of one simulation.  Written only by
-// the controller kernel (and the host between launches); the step kernel
-// reads it and raises smax_bits / flags atomically.
+// the launch that closes a run of attempts (and the host between launches);
+// the step kernel reads it and raises smax_bits / flags atomically.
 struct Clock {
     double t;                    // time of the current state (dx/c0 units)
     double dt;                   // step of the next attempt
@@ -78,12 +78,9 @@ struct Clock {
 // nu = dt max|s|; nu > cfl_max rejects (state kept, dt *= nu_W/nu, at most
 // max_retries in a row), otherwise the step is accepted, t += dt, the buffer
 // holding the new state (cur + 1 modulo nbuf) becomes current and, unless
-// the time step is fixed, dt *= nu_W/nu.  All memory traffic is issued at
-// once, so the launch costs one round trip: the attempt's largest speed and
-// flags are taken (and cleared for the next attempt) whether or not the
-// attempt counts -- a step launch that had nothing to do left them at zero.
-// The decision itself, as a function: the clock state h an attempt ran with,
-// the bits of its largest wave speed and its flags -> the state after it.
+// the time step is fixed, dt *= nu_W/nu.  A function of the clock state h an
+// attempt ran with, the bits of its largest wave speed and its flags; an
+// attempt that had nothing to do changes nothing.
 __device__ __forceinline__ Clock control_next(Clock h, unsigned long long sb, unsigned flags, int fixed_dt,
                                               double cfl_target, double cfl_max, int max_retries, int nbuf)
 {
@@ -121,16 +118,6 @@ __device__ __forceinline__ Clock control_next(Clock h, unsigned long long sb, un
     h.nu_m2 = h.nu_m2 + dev * (nu - mean);
     if (!fixed_dt && smax > 0.0) h.dt = dt * cfl_target / nu;
     return h;
-}
-
-__device__ __forceinline__ void control_attempt(Clock* c, int fixed_dt, double cfl_target, double cfl_max,
-                                                int max_retries, int nbuf)
-{
-    const unsigned long long sb = atomicExch(&c->smax_bits, 0ull);
-    const unsigned flags = atomicExch(&c->flags, 0u);
-    const Clock h = *c;
-    if (h.status != 0 || h.accepted >= h.target) return;
-    *c = control_next(h, sb, flags, fixed_dt, cfl_target, cfl_max, max_retries, nbuf);
 }
 
 // Attempts that take the previous attempt's decision in their own prologue

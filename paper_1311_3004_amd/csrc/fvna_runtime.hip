@@ -31,15 +31,6 @@ using namespace fvna;
 // Kernels
 // ---------------------------------------------------------------------------
 
-// Accept or reject the attempt just made (control_attempt of
-// fvna_device.hpp), one thread per simulation.  (Deciding in the step kernel's
-// last wavefront instead needs an agent-scope release fence in every
-// wavefront, which writes back the L2 and cost more than a launch.)
-__device__ __forceinline__ void control(const SimDesc& d)
-{
-    control_attempt(d.clk, d.fixed_dt, d.cfl_target, d.cfl_max, d.max_retries, 2);
-}
-
 __global__ void k_ctrl_fold(SimDesc d, int last, long long owed)
 {
     if (threadIdx.x == 0) *d.clk = fold_decision(d, last, owed);
@@ -115,10 +106,11 @@ __global__ __launch_bounds__(256) void k_close(SimDesc d, RecDesc r, int last, l
     }
 }
 
-__global__ void k_ctrl_batch(const SimDesc* __restrict__ descs, int n)
+// The same for every simulation of a batch.
+__global__ void k_fold_batch(const SimDesc* __restrict__ descs, int n, int last, long long owed)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n) control(descs[k]);
+    if (k < n) *descs[k].clk = fold_decision(descs[k], last, owed);
 }
 
 __global__ void k_bump(Clock* c, long long n)
@@ -498,10 +490,10 @@ fvna_status fail(fvna_status s, const std::string& msg)
 constexpr size_t ALIGN = 256;
 constexpr size_t STAGE_CELLS = size_t(1) << 20;   // staging chunk for set/get state
 constexpr int GRAPH_CHUNK = 32;                   // attempts per captured graph
-// Segment height of batched simulations without their own: the batch runs in
-// several rounds of wavefronts, so the one-round rule of a single grid does not
-// apply; 128 rows measured best on 64 uneven grids (48..256 tried).
-constexpr int BATCH_TILE_ROWS = 128;
+// Segment height of batched simulations without their own when the batch runs
+// in several rounds of wavefronts: 64 uneven grids, us per step at 48 / 64 / 96
+// / 128 rows 806 / 793 / 782 / 812.  Smaller batches: batch_rows.
+constexpr int BATCH_TILE_ROWS = 96;
 
 constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -653,6 +645,12 @@ struct Plan { int rows; double us; };
 // (within 8% over 720^2 .. 4096^2), and the least is taken: FP32 1000^2 n = 1
 // 21.8 us per step (n = 2: 28), 2000^2 n = 2 43.2 (n = 1: 66, n = 3: 50), 4096^2
 // n = 3 135 (n = 2: 151).  Never fewer than 8 rows.
+const double* row_cost(bool f64, int n)
+{
+    static const double d[][2] = {{5.0, 0.95}, {5.0, 1.53}}, f[][2] = {{4.0, 0.70}, {4.5, 0.93}, {12.0, 1.20}};
+    return f64 ? d[n - 1] : f[n - 1];
+}
+
 Plan segment_plan(const fvna_params* p, int cu_count)
 {
     const long long strips = (p->nx + OUTW - 1) / OUTW;
@@ -670,17 +668,41 @@ Plan segment_plan(const fvna_params* p, int cu_count)
         }
         return tr;
     };
-    static const double f64[][2] = {{5.0, 0.95}, {5.0, 1.53}}, f32[][2] = {{4.0, 0.70}, {4.5, 0.93}, {12.0, 1.20}};
     const bool d = p->precision == FVNA_F64;
     const int most = d ? Occupancy<double>::waves : Occupancy<float>::waves;
     Plan best{0, 1e30};
     for (int n = 1; n <= most; ++n) {
         const long long tr = rows_for((long long)std::max(cu_count, 1) * 4 * n);
-        const double* c = d ? f64[n - 1] : f32[n - 1];
+        const double* c = row_cost(d, n);
         const double us = c[0] + c[1] * (double)(tr + 2 * HALO);
         if (us < best.us) best = Plan{(int)tr, us};
     }
     return best;
+}
+
+// Segment height of a batch's members (those without their own): a batch that
+// fits the device in one round of wavefronts is one wide grid to it, and the
+// same costs choose between one, two and three wavefronts per SIMD (us per step
+// against 128 rows throughout: 12 FP32 grids of 256 .. 1024 cells a side, 52
+// rows, 69 / 135; 9 FP64 grids of 96 .. 256, 8 rows, 22 / 166).
+int batch_rows(const fvna_params* p, int n, int cu_count)
+{
+    const bool d = p[0].precision == FVNA_F64;
+    const int most = d ? Occupancy<double>::waves : Occupancy<float>::waves;
+    Plan best{BATCH_TILE_ROWS, 1e30};             // several rounds, unless one is enough
+    for (int w = 1; w <= most; ++w) {
+        const long long slots = 4ll * std::max(cu_count, 1) * w;
+        for (int rows = 8; rows < BATCH_TILE_ROWS; ++rows) {
+            long long waves = 0;
+            for (int k = 0; k < n; ++k)
+                waves += (long long)((p[k].nx + OUTW - 1) / OUTW) * ((p[k].ny + rows - 1) / rows);
+            if (waves > slots) continue;
+            const double us = row_cost(d, w)[0] + row_cost(d, w)[1] * (rows + 2 * HALO);
+            if (us < best.us) best = Plan{rows, us};
+            break;
+        }
+    }
+    return best.rows;
 }
 
 // Block tiles: T = BLOCK_ROWS B - 6 rows take B batches; a CU holds two blocks
@@ -732,7 +754,7 @@ std::map<std::tuple<int, int, int, int>, int> g_tune;
 
 struct Launcher {
     void (*step)(const SimDesc&, const RecDesc&, int force, int pos, long long owed, hipStream_t);
-    void (*step_batch)(const SimDesc*, const TileRef*, int ntiles, int force, hipStream_t);
+    void (*step_batch)(const SimDesc*, const TileRef*, int ntiles, int force, int pos, long long owed, hipStream_t);
     void (*dry)(const SimDesc&, hipStream_t);
     void (*imp)(const SimDesc&, const double*, int, int, int, double, int, hipStream_t);
     void (*exp)(const SimDesc&, double*, int, int, int, int, int, double, hipStream_t);
@@ -757,9 +779,11 @@ Launcher make_launcher()
         const int blocks = (tiles + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
         hipLaunchKernelGGL((k_step<S, T, AXI>), dim3(blocks + r.on), dim3(256), 0, s, d, r, force, pos, owed);
     };
-    L.step_batch = [](const SimDesc* descs, const TileRef* tiles, int ntiles, int force, hipStream_t s) {
+    L.step_batch = [](const SimDesc* descs, const TileRef* tiles, int ntiles, int force, int pos, long long owed,
+                      hipStream_t s) {
         const int blocks = (ntiles + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
-        hipLaunchKernelGGL((k_step_batch<S, T, AXI>), dim3(blocks), dim3(256), 0, s, descs, tiles, ntiles, force);
+        hipLaunchKernelGGL((k_step_batch<S, T, AXI>), dim3(blocks), dim3(256), 0, s, descs, tiles, ntiles, force, pos,
+                           owed);
     };
     L.dry = [](const SimDesc& d, hipStream_t s) {
         hipLaunchKernelGGL((k_dry<S, T>), dim3((d.nx + 1 + 255) / 256, std::min(d.ny + 1, 64)), dim3(256), 0, s, d);
@@ -1599,14 +1623,20 @@ void batch_tiles(const fvna_batch* b, std::vector<TileRef>& tiles)
 
 }  // namespace
 
+// n attempts in a row of the whole batch and the closing decisions, as
+// launch_attempts for one simulation.
+static void batch_attempts(fvna_batch* b, int n, long long owed, hipStream_t s)
+{
+    if (n <= 0) return;
+    for (int k = 0; k < n; ++k) b->L.step_batch(b->d_desc, b->d_tiles, b->ntiles, 0, k, owed, s);
+    hipLaunchKernelGGL(k_fold_batch, dim3((b->n + 63) / 64), dim3(64), 0, s, b->d_desc, b->n, n - 1, owed);
+}
+
 static fvna_status batch_graph(fvna_batch* b)
 {
     if (b->exec) return FVNA_OK;
     HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < GRAPH_CHUNK; ++k) {
-        b->L.step_batch(b->d_desc, b->d_tiles, b->ntiles, 0, b->cap);
-        hipLaunchKernelGGL(k_ctrl_batch, dim3((b->n + 63) / 64), dim3(64), 0, b->cap, b->d_desc, b->n);
-    }
+    batch_attempts(b, GRAPH_CHUNK, 0, b->cap);
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamEndCapture(b->cap, &g));
     b->graph = g;
@@ -1655,13 +1685,13 @@ fvna_status fvna_batch_create(int32_t n, const fvna_params* per_sim, void* const
         auto it = g_btune.find(batch_key(per_sim, n));
         if (it != g_btune.end()) tuned = it->second;
     }
+    const int rows = batch_rows(per_sim, n, device_cu_count());
     for (int k = 0; k < n; ++k) {
         const fvna_params& p = per_sim[k];
         b->p.push_back(p);
         SimDesc d;
-        // many simulations fill the device in many rounds: moderate segments
-        // (or the heights fvna_batch_autotune chose for this composition)
-        int tr = p.tile_rows ? p.tile_rows : (tuned.empty() ? BATCH_TILE_ROWS : tuned[k]);
+        // or the heights fvna_batch_autotune chose for this composition
+        int tr = p.tile_rows ? p.tile_rows : (tuned.empty() ? rows : tuned[k]);
         char* sc = (char*)bufs[3 * k + 2];
         fill_desc(d, &p, bufs[3 * k], bufs[3 * k + 1], (Clock*)(sc + OFF_CLOCK), tr, false);
         const fvna_status sr = fill_rinv(d, &p, sc, b->stream);
@@ -1721,15 +1751,14 @@ fvna_status fvna_batch_set_state(fvna_batch* b, int32_t k, const double* rho_p, 
     return fvna_set_state(&c, rho_p, mom_x, mom_y);
 }
 
-static fvna_status batch_enqueue(fvna_batch* b, long long attempts)
+static fvna_status batch_enqueue(fvna_batch* b, long long attempts, long long owed = 0)
 {
-    fvna_status s = batch_graph(b);
-    if (s) return s;
-    for (long long k = 0; k < attempts / GRAPH_CHUNK; ++k) HIP_TRY(hipGraphLaunch(b->exec, b->stream));
-    for (long long k = 0; k < attempts % GRAPH_CHUNK; ++k) {
-        b->L.step_batch(b->d_desc, b->d_tiles, b->ntiles, 0, b->stream);
-        hipLaunchKernelGGL(k_ctrl_batch, dim3((b->n + 63) / 64), dim3(64), 0, b->stream, b->d_desc, b->n);
+    if (attempts >= GRAPH_CHUNK) {
+        const fvna_status s = batch_graph(b);
+        if (s) return s;
+        for (long long k = 0; k < attempts / GRAPH_CHUNK; ++k) HIP_TRY(hipGraphLaunch(b->exec, b->stream));
     }
+    batch_attempts(b, (int)(attempts % GRAPH_CHUNK), owed, b->stream);
     HIP_TRY(hipGetLastError());
     return FVNA_OK;
 }
@@ -1739,6 +1768,7 @@ fvna_status fvna_batch_step(fvna_batch* b, int64_t nsteps)
     if (!b) return fail(FVNA_E_INVALID, "batch is NULL");
     if (nsteps < 0) return fail(FVNA_E_INVALID, "nsteps must be >= 0");
     if (nsteps == 0) return FVNA_OK;
+    if (nsteps < GRAPH_CHUNK) return batch_enqueue(b, nsteps, nsteps);
     hipLaunchKernelGGL(k_bump_batch, dim3((b->n + 63) / 64), dim3(64), 0, b->stream, b->d_desc, b->n,
                        (long long)nsteps);
     HIP_TRY(hipGetLastError());
@@ -1893,7 +1923,7 @@ fvna_status fvna_batch_time_step_kernel(fvna_batch* b, int32_t reps, double* ms_
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
     HIP_TRY(hipEventRecord(e0, b->stream));
-    for (int k = 0; k < reps; ++k) b->L.step_batch(b->d_desc, b->d_tiles, b->ntiles, 1, b->stream);
+    for (int k = 0; k < reps; ++k) b->L.step_batch(b->d_desc, b->d_tiles, b->ntiles, 1, 0, 0, b->stream);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(e1, b->stream));
     HIP_TRY(hipEventSynchronize(e1));

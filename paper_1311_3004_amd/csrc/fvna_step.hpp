@@ -231,19 +231,22 @@ void k_step_block(SimDesc d, RecDesc r, int force, int pos, long long owed)
 
 struct TileRef { int sim, strip, seg, pad; };
 
+// One attempted step of every simulation of a batch; each tile takes its own
+// simulation's decision as k_step does, and a simulation's first tile closes it.
 template <typename S, typename T, int AXI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Occupancy<T>::waves)))
-void k_step_batch(const SimDesc* __restrict__ descs, const TileRef* __restrict__ tiles, int ntiles, int force)
+void k_step_batch(const SimDesc* __restrict__ descs, const TileRef* __restrict__ tiles, int ntiles, int force, int pos,
+                  long long owed)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK + wave;
     if (tile >= ntiles) return;
+    pos = max(pos, 0);
     const TileRef tr = tiles[tile];
     const SimDesc& d = descs[tr.sim];
-    Clock* clk = d.clk;
-    const Clock h = *clk;
-    if (!force && (h.status != 0 || h.accepted >= h.target)) return;
-    march_tile<S, T, AXI>(d, tr.strip, tr.seg, attempt_of(h, &clk->smax_bits, &clk->flags));
+    Attempt at;
+    if (step_begin(d, force, pos, owed, at)) march_tile<S, T, AXI>(d, tr.strip, tr.seg, at);
+    if (tr.strip == 0 && tr.seg == 0 && (threadIdx.x & (WAVE - 1)) == 0) step_end(d, pos, owed);
 }
 
 }  // namespace fvna
