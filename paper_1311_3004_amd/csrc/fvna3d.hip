@@ -98,11 +98,11 @@ template <typename T> struct Q4 { T R, n, a, b; };
 // (0, 0, 1, 0) and (0, 0, 0, 1); strengths from sum_p alpha^p r^p = Q_R - Q_L.
 // The means are carried as sums of the two sides (every factor 2 cancels).
 // Returns the interface's largest |s| in the form Cfl<T> reduces (FP32 as an
-// excess over 1) and the discriminant in D.
+// excess over 1), the discriminant in D, and in parted whether |w| < c (roe_sh).
 // h = 1/(2 + L.R + R.R) comes from the caller (rcp_pair).
 template <typename T>
 __device__ __forceinline__ T roe4(const Q4<T>& L, T unL, T uaL, T ubL, const Q4<T>& R, T unR, T uaR, T ubR,
-                                  T beta, T h, W4<T>& w, T& D)
+                                  T beta, T h, W4<T>& w, T& D, bool& parted)
 {
     const T Sr = L.R + R.R, Sn = unL + unR, Sa = uaL + uaR, Sb = ubL + ubR;
     const T wv = Sn * h;
@@ -113,6 +113,7 @@ __device__ __forceinline__ T roe4(const Q4<T>& L, T unL, T uaL, T ubL, const Q4<
     T spd;
     if constexpr (sizeof(T) == 8) spd = c + abs_(wv);
     else spd = fma_(D1, rcp(T(1) + c), abs_(wv));
+    parted = abs_(wv) < c;
     w.s1 = wv + c;
     w.s2 = wv - c;
     w.s3 = wv;
@@ -148,36 +149,37 @@ __device__ __forceinline__ void cross4(const W4<T>& x, const W4<T>& y, T tx[4], 
 // fluc:p, limiter, fv-hr): Gm = A^- dQ + F~ for the cell on the low side,
 // Gp = A^+ dQ - F~ for the cell on the high side.  lo/hi: upwind values t of
 // the interface below/above (cross4).  The upwind interface is the one below
-// for s >= 0.  The limited products psi alpha as in two dimensions (hr_split):
+// for s >= 0.  The limited products and PARTED as in two dimensions (hr_split):
 // FP64 from u = t / n with one reciprocal of n1 n2, FP32 from
 // theta = t / (alpha n).
-template <typename T>
+template <bool PARTED, typename T>
 __device__ __forceinline__ void hr_split4(const W4<T>& w, const T lo[4], const T hi[4], T dt, T Gm[4], T Gp[4])
 {
-    const bool n1 = w.s1 < T(0), n2 = w.s2 < T(0), n3 = w.s3 < T(0);
-    const T t1 = n1 ? hi[0] : lo[0], t2 = n2 ? hi[1] : lo[1];
+    const bool n3 = w.s3 < T(0);
+    const T t1 = PARTED ? lo[0] : w.s1 < T(0) ? hi[0] : lo[0], t2 = PARTED ? hi[1] : w.s2 < T(0) ? hi[1] : lo[1];
     const T t3 = n3 ? hi[2] : lo[2], t4 = n3 ? hi[3] : lo[3];
     const T q1 = fma_(w.r1b, w.r1b, fma_(w.r1a, w.r1a, fma_(w.s1, w.s1, T(1))));
     const T q2 = fma_(w.r2b, w.r2b, fma_(w.r2a, w.r2a, fma_(w.s2, w.s2, T(1))));
-    T pa1, pa2, pa3, pa4;
+    const T as1 = abs_(w.s1), as2 = abs_(w.s2), as3 = abs_(w.s3);
+    T c1, c2, c3, c4;
     if constexpr (sizeof(T) == 8) {
         const T ip = rcp(q1 * q2);
-        pa1 = mc_scaled(w.a1, t1 * (ip * q2));
-        pa2 = mc_scaled(w.a2, t2 * (ip * q1));
-        pa3 = mc_scaled(w.a3, t3);
-        pa4 = mc_scaled(w.a4, t4);
+        const T hdt = T(-0.5) * dt;
+        const T f3 = fma_(hdt, as3, T(0.5)) * as3;
+        c1 = (fma_(hdt, as1, T(0.5)) * as1) * mc_scaled(w.a1, t1 * (ip * q2));
+        c2 = (fma_(hdt, as2, T(0.5)) * as2) * mc_scaled(w.a2, t2 * (ip * q1));
+        c3 = f3 * mc_scaled(w.a3, t3);
+        c4 = f3 * mc_scaled(w.a4, t4);
     } else {
-        pa1 = mc_half(t1 * rcp(w.a1 * q1)) * w.a1;
-        pa2 = mc_half(t2 * rcp(w.a2 * q2)) * w.a2;
-        pa3 = mc_unit(w.a3, t3);
-        pa4 = mc_unit(w.a4, t4);
+        const T f3 = fma_(-dt, as3, T(1)) * as3;
+        c1 = (fma_(-dt, as1, T(1)) * as1) * (mc_half(t1 * rcp(w.a1 * q1)) * w.a1);
+        c2 = (fma_(-dt, as2, T(1)) * as2) * (mc_half(t2 * rcp(w.a2 * q2)) * w.a2);
+        c3 = f3 * mc_unit(w.a3, t3);
+        c4 = f3 * mc_unit(w.a4, t4);
     }
-    const T as1 = abs_(w.s1), as2 = abs_(w.s2), as3 = abs_(w.s3);
-    const T f1 = fma_(-dt, as1, T(1)) * as1, f2 = fma_(-dt, as2, T(1)) * as2, f3 = fma_(-dt, as3, T(1)) * as3;
-    const T c1 = f1 * pa1, c2 = f2 * pa2, c3 = f3 * pa3, c4 = f3 * pa4;
     const T m3 = min_(w.s3, T(0));
-    const T e1 = fma_(min_(w.s1, T(0)), w.a1, c1);
-    const T e2 = fma_(min_(w.s2, T(0)), w.a2, c2);
+    const T e1 = PARTED ? c1 : fma_(min_(w.s1, T(0)), w.a1, c1);
+    const T e2 = fma_(PARTED ? w.s2 : min_(w.s2, T(0)), w.a2, c2);
     const T e3 = fma_(m3, w.a3, c3);
     const T e4 = fma_(m3, w.a4, c4);
     const T g1 = fma_(w.s1, w.a1, -e1);
@@ -199,6 +201,7 @@ __device__ __forceinline__ void hr_split4(const W4<T>& w, const T lo[4], const T
 template <typename T> struct March4 {
     Q4<T> q; T un, ua, ub;     // last cell pushed and its velocities
     W4<T> w;                   // interface below it
+    bool parted;               // hr_split's PARTED holds there in every lane
     T lo[4];                   // upwind values t of the interface below it for it (cross4)
     Q4<T> part;                // previous cell minus dt Gp of its lower interface (awaiting its upper flux)
 };
@@ -210,6 +213,7 @@ __device__ __forceinline__ void march_zero(March4<T>& m)
     m.q = {z, z, z, z};
     m.un = m.ua = m.ub = z;
     m.w = {z, z, z, z, z, z, z, z, z, z, z};
+    m.parted = false;
     m.lo[0] = m.lo[1] = m.lo[2] = m.lo[3] = z;
     m.part = {z, z, z, z};
 }
@@ -226,12 +230,18 @@ __device__ __forceinline__ void march_push(const Q4<T>& q, const March4<T>& in, 
     const T un = q.n * ir, ua = q.a * ir, ub = q.b * ir;
     W4<T> wA;
     T D;
-    const T spd = roe4(in.q, in.un, in.ua, in.ub, q, un, ua, ub, beta, h, wA, D);
-    if (count) acc.add(spd, D);
+    bool parted;
+    const T spd = roe4(in.q, in.un, in.ua, in.ub, q, un, ua, ub, beta, h, wA, D, parted);
+    out.parted = all_lanes(parted);
+    if (count) {
+        if (__builtin_expect(out.parted, 1)) acc.add(spd);
+        else acc.add(spd, D);
+    }
     T tup[4], hi[4];
     cross4(in.w, wA, tup, hi);
     T Gm[4], Gp[4];
-    hr_split4(in.w, in.lo, hi, dt, Gm, Gp);
+    if (__builtin_expect(in.parted, 1)) hr_split4<true>(in.w, in.lo, hi, dt, Gm, Gp);
+    else hr_split4<false>(in.w, in.lo, hi, dt, Gm, Gp);
     done.R = fma_(-dt, Gm[0], in.part.R);
     done.n = fma_(-dt, Gm[1], in.part.n);
     done.a = fma_(-dt, Gm[2], in.part.a);
@@ -381,18 +391,33 @@ __device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Att
         const T unL = from_lo(un), uaL = from_lo(ua), ubL = from_lo(ub);
         W4<T> wv;
         T D;
-        const T spd = roe4(L, unL, uaL, ubL, q, un, ua, ub, beta, h, wv, D);
-        xacc.add(spd, D);
-        W4<T> wr;
-        wr.a1 = from_hi(wv.a1); wr.s1 = from_hi(wv.s1); wr.r1a = from_hi(wv.r1a); wr.r1b = from_hi(wv.r1b);
-        wr.a2 = from_hi(wv.a2); wr.s2 = from_hi(wv.s2); wr.r2a = from_hi(wv.r2a); wr.r2b = from_hi(wv.r2b);
-        wr.a3 = from_hi(wv.a3);
-        wr.a4 = from_hi(wv.a4);
-        T tup[4], hi[4], lo[4];
-        cross4(wv, wr, tup, hi);
-        lo[0] = from_lo(tup[0]); lo[1] = from_lo(tup[1]); lo[2] = from_lo(tup[2]); lo[3] = from_lo(tup[3]);
-        T Gm[4], Gp[4];
-        hr_split4(wv, lo, hi, dt, Gm, Gp);
+        bool parted;
+        const T spd = roe4(L, unL, uaL, ubL, q, un, ua, ub, beta, h, wv, D, parted);
+        T hi[4], lo[4], Gm[4], Gp[4];
+        if (__builtin_expect(all_lanes(parted), 1)) {
+            xacc.add(spd);
+            // family 1 meets the interface to the left, family 2 the one to the right
+            const T x1 = fma_(from_lo(wv.r1b), wv.r1b,
+                              fma_(from_lo(wv.r1a), wv.r1a, fma_(from_lo(wv.s1), wv.s1, T(1))));
+            const T x2 = fma_(wv.r2b, from_hi(wv.r2b),
+                              fma_(wv.r2a, from_hi(wv.r2a), fma_(wv.s2, from_hi(wv.s2), T(1))));
+            lo[0] = from_lo(wv.a1) * x1;
+            hi[1] = from_hi(wv.a2) * x2;
+            lo[2] = from_lo(wv.a3); hi[2] = from_hi(wv.a3);
+            lo[3] = from_lo(wv.a4); hi[3] = from_hi(wv.a4);
+            hr_split4<true>(wv, lo, hi, dt, Gm, Gp);
+        } else {
+            xacc.add(spd, D);
+            W4<T> wr;
+            wr.a1 = from_hi(wv.a1); wr.s1 = from_hi(wv.s1); wr.r1a = from_hi(wv.r1a); wr.r1b = from_hi(wv.r1b);
+            wr.a2 = from_hi(wv.a2); wr.s2 = from_hi(wv.s2); wr.r2a = from_hi(wv.r2a); wr.r2b = from_hi(wv.r2b);
+            wr.a3 = from_hi(wv.a3);
+            wr.a4 = from_hi(wv.a4);
+            T tup[4];
+            cross4(wv, wr, tup, hi);
+            lo[0] = from_lo(tup[0]); lo[1] = from_lo(tup[1]); lo[2] = from_lo(tup[2]); lo[3] = from_lo(tup[3]);
+            hr_split4<false>(wv, lo, hi, dt, Gm, Gp);
+        }
         Q4<T> o2;
         o2.R = fma_(-dt, from_hi(Gm[0]) + Gp[0], q.R);
         o2.n = fma_(-dt, from_hi(Gm[1]) + Gp[1], q.n);

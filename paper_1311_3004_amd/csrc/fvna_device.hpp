@@ -365,10 +365,12 @@ template <typename T> struct Wave { T s1, s2, s3, a1, a2, a3, r1, r2; };
 // excess (so ~1e-10 on the speed itself) -- and the discriminant D in D.
 // When D is not a positive finite number the returned value is meaningless
 // (FP32: always NaN); Cfl::add sorts these cases out.
+// parted: |w| < c, so s^1 > 0 > s^2 (hr_split); false whenever D is not a
+// positive finite number.
 // roe_sh takes Sr = RL + RR and h = 1/(2 + Sr) from the caller (rcp_pair).
 template <typename T>
 __device__ __forceinline__ T roe_sh(T RL, T nL, T tL, T vnL, T vtL,
-                                    T RR, T nR, T tR, T vnR, T vtR, T beta, T Sr, T h, Wave<T>& w, T& D)
+                                    T RR, T nR, T tR, T vnR, T vtR, T beta, T Sr, T h, Wave<T>& w, T& D, bool& parted)
 {
     // Sums of the two sides stand for the means (Zbar^1 - 1 = Sr/2, zn = Sn/2,
     // zt = St/2); every factor of 2 they introduce cancels exactly.
@@ -382,6 +384,7 @@ __device__ __forceinline__ T roe_sh(T RL, T nL, T tL, T vnL, T vtL,
     T spd;
     if constexpr (sizeof(T) == 8) spd = c + abs_(wv);
     else spd = fma_(D1, rcp(T(1) + c), abs_(wv));
+    parted = abs_(wv) < c;
     w.s1 = wv + c;
     w.s2 = wv - c;
     w.s3 = wv;
@@ -399,8 +402,12 @@ __device__ __forceinline__ T roe(T RL, T nL, T tL, T vnL, T vtL,
                                  T RR, T nR, T tR, T vnR, T vtR, T beta, Wave<T>& w, T& D)
 {
     const T Sr = RL + RR;
-    return roe_sh(RL, nL, tL, vnL, vtL, RR, nR, tR, vnR, vtR, beta, Sr, rcp(T(2) + Sr), w, D);
+    bool parted;
+    return roe_sh(RL, nL, tL, vnL, vtL, RR, nR, tR, vnR, vtR, beta, Sr, rcp(T(2) + Sr), w, D, parted);
 }
+
+// Whether p holds in every lane of the wavefront (a scalar, to branch on).
+__device__ __forceinline__ bool all_lanes(bool p) { return __builtin_amdgcn_ballot_w64(!p) == 0; }
 
 // 1/a and 1/b for the two positive factors a = 1 + R of a cell and
 // b = 2 + Sr of an interface it borders: FP64 from one reciprocal of a b
@@ -448,6 +455,8 @@ template <> struct Cfl<float> {
         m = __builtin_elementwise_maximum(m, spd);
         dmin = __builtin_elementwise_minimum(dmin, D);
     }
+    // an interface with D known to be positive and finite (roe_sh: parted)
+    __device__ __forceinline__ void add(float spd) { m = __builtin_elementwise_maximum(m, spd); }
     // This lane's contribution if it holds real interfaces (else nothing).
     __device__ __forceinline__ void finish(bool counted, float& spd, bool& nonhyp, bool& nonfin) const
     {
@@ -469,6 +478,7 @@ template <> struct Cfl<double> {
         h = h || __builtin_amdgcn_class(D, NOT_POSITIVE);
         f = f || __builtin_amdgcn_class(D, POS_INF);
     }
+    __device__ __forceinline__ void add(double spd) { m = __builtin_fmax(m, spd); }
     __device__ __forceinline__ void finish(bool counted, double& spd, bool& nonhyp, bool& nonfin) const
     {
         nonhyp = counted && h;
@@ -480,8 +490,8 @@ template <> struct Cfl<double> {
 // MC limiter (Sec. 3.1), phi(theta) = max(0, min((1 + theta)/2, 2, 2 theta)),
 // with theta = (W_up . W) / (W . W) for the waves W^p = alpha^p r^p,
 // r^p = (1, s^p, r^p) of families p = 1, 2 and r^3 = (0, 0, 1).  The scheme
-// needs theta only through the product phi(theta) alpha, and only half of it
-// (hr_split doubles the factor it multiplies): psi alpha with psi = phi/2 =
+// needs theta only through the product phi(theta) alpha, and FP32 only half of
+// it (hr_split doubles the factor it multiplies): psi alpha with psi = phi/2 =
 // max(0, min((1 + theta)/4, 1, theta)).
 //
 // With X = r^p_up . r^p and n = r^p . r^p (>= 1), alpha cancels from the
@@ -500,25 +510,27 @@ __device__ __forceinline__ T mc_half(T th)
     return max_(T(0), min_(min_(fma_(T(0.25), th, T(0.25)), T(1)), th));
 }
 
-// FP64: psi alpha directly from alpha and u = alpha theta = t / n, with no
-// division by alpha.  Scaling the min/max by alpha (and flipping them when
-// alpha < 0) gives, with g the sign of alpha,
-//   psi alpha = g max(0, min((|alpha| + g u)/4, |alpha|, g u)),
-// which is 0 for alpha = 0.  g u is formed as u * copysign(1, alpha), exact,
-// and a multiply's result, which the compiler knows to be a canonical
-// number (min/max in IEEE mode need canonical operands; a bit flip would
-// cost a quieting instruction at each of them); the result takes alpha's
-// sign by copysign; /4 is exact (ldexp).  1/n is needed for families 1 and 2
-// only (n = 1 for family 3), and both come from one reciprocal of
-// n1 n2 >= 1 (hr_split).  This saves the three reciprocals of alpha^p n^p --
-// on this chip an FP64 reciprocal estimate occupies the SIMD four times as
-// long as an FMA.
+// FP64: phi alpha directly from alpha and u = alpha theta = t / n, with no
+// division by alpha: where alpha and u have one sign, phi alpha is twice
+//   min(|alpha + u|/4, |alpha|, |u|)
+// with that sign, and 0 where they differ.  Both halves of the sum
+// copysign(m, alpha) + copysign(m, u) carry m then, or cancel.  1/n is needed
+// for families 1 and 2 only (n = 1 for family 3), and both come from one
+// reciprocal of n1 n2 >= 1 (hr_split).  This saves the three reciprocals of
+// alpha^p n^p -- on this chip an FP64 reciprocal estimate occupies the SIMD
+// four times as long as an FMA.  The minima are written as instructions: u
+// comes off a lane shift or LDS, where the compiler would quiet it first (a
+// signalling NaN, which no arithmetic makes) at one more instruction each.
+__device__ __forceinline__ double min_abs(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
 __device__ __forceinline__ double mc_scaled(double a, double u)
 {
-    const double gu = u * __builtin_copysign(1.0, a);
-    const double aa = __builtin_fabs(a);
-    const double m = max_(0.0, min_(min_(__builtin_ldexp(aa + gu, -2), aa), gu));
-    return __builtin_copysign(m, a);
+    const double m = min_abs(min_abs((a + u) * 0.25, a), u);
+    return __builtin_copysign(m, a) + __builtin_copysign(m, u);
 }
 
 // FP32, a family whose eigenvector is a unit vector (n = 1, X = 1: the shear
@@ -559,35 +571,43 @@ __device__ __forceinline__ void wave_cross(const Wave<T>& a, const Wave<T>& b, T
 // eqs. fluc:m, fluc:p, limiter, fv-hr.  The upwind interface of family p is
 // the one below when s^p >= 0 and the one above when s^p < 0.  Components in
 // split-local order (density, normal, tangential momentum).
-template <typename T>
+//
+// PARTED: s^1 > 0 > s^2 is known (roe_sh), as it is wherever the flow is slower
+// than sound: family 1 then takes its upwind value from below and family 2 from
+// above, dlo[1] and dhi[0] are not looked at (so need not be formed or
+// shipped), and min(s, 0) is 0 and s^2.  A sweep branches on it for the whole
+// wavefront; both forms give the same values.  About a tenth of the issued
+// instructions (and of the lane shifts) go; the step takes, with / without:
+// FP64 4096^2 240 / 248 us, 256^2 10.3 / 10.7, axisymmetric FP32 8192 x 2048
+// 146 / 154, FP16 2051 x 1027 33.5 / 37.3, 3-D FP32 256^3 306 / 319.  A march
+// with no branch that repeats a tile on finding other waves is no faster (FP64
+// 4096^2 level, FP32 8192 x 2048 2% slower).
+template <bool PARTED, typename T>
 __device__ __forceinline__ void hr_split(const Wave<T>& w, const T dlo[3], const T dhi[3], T dt,
                                          T Gm[3], T Gp[3])
 {
-    const T t1 = w.s1 < T(0) ? dhi[0] : dlo[0];
-    const T t2 = w.s2 < T(0) ? dhi[1] : dlo[1];
+    const T t1 = PARTED ? dlo[0] : w.s1 < T(0) ? dhi[0] : dlo[0];
+    const T t2 = PARTED ? dhi[1] : w.s2 < T(0) ? dhi[1] : dlo[1];
     const T t3 = w.s3 < T(0) ? dhi[2] : dlo[2];
     const T n1 = fma_(w.r1, w.r1, fma_(w.s1, w.s1, T(1)));
     const T n2 = fma_(w.r2, w.r2, fma_(w.s2, w.s2, T(1)));
-    // pa_p = psi^p alpha^p
-    T pa1, pa2, pa3;
+    const T as1 = abs_(w.s1), as2 = abs_(w.s2), as3 = abs_(w.s3);
+    // correction strengths c_p = 1/2 |s| (1 - dt |s|) phi alpha
+    T c1, c2, c3;
     if constexpr (sizeof(T) == 8) {
         const T ip = rcp(n1 * n2);
-        pa1 = mc_scaled(w.a1, t1 * (ip * n2));
-        pa2 = mc_scaled(w.a2, t2 * (ip * n1));
-        pa3 = mc_scaled(w.a3, t3);
+        const T hdt = T(-0.5) * dt;
+        c1 = (fma_(hdt, as1, T(0.5)) * as1) * mc_scaled(w.a1, t1 * (ip * n2));
+        c2 = (fma_(hdt, as2, T(0.5)) * as2) * mc_scaled(w.a2, t2 * (ip * n1));
+        c3 = (fma_(hdt, as3, T(0.5)) * as3) * mc_scaled(w.a3, t3);
     } else {
-        pa1 = mc_half(t1 * rcp(w.a1 * n1)) * w.a1;
-        pa2 = mc_half(t2 * rcp(w.a2 * n2)) * w.a2;
-        pa3 = mc_unit(w.a3, t3);
+        c1 = (fma_(-dt, as1, T(1)) * as1) * (mc_half(t1 * rcp(w.a1 * n1)) * w.a1);
+        c2 = (fma_(-dt, as2, T(1)) * as2) * (mc_half(t2 * rcp(w.a2 * n2)) * w.a2);
+        c3 = (fma_(-dt, as3, T(1)) * as3) * mc_unit(w.a3, t3);
     }
-    const T as1 = abs_(w.s1), as2 = abs_(w.s2), as3 = abs_(w.s3);
-    // correction strengths c_p = 1/2 |s| (1 - dt |s|) phi alpha = |s| (1 - dt |s|) psi alpha
-    const T c1 = (fma_(-dt, as1, T(1)) * as1) * pa1;
-    const T c2 = (fma_(-dt, as2, T(1)) * as2) * pa2;
-    const T c3 = (fma_(-dt, as3, T(1)) * as3) * pa3;
     // e_p = min(s,0) alpha + c_p ; g_p = max(s,0) alpha - c_p = s alpha - e_p
-    const T e1 = fma_(min_(w.s1, T(0)), w.a1, c1);
-    const T e2 = fma_(min_(w.s2, T(0)), w.a2, c2);
+    const T e1 = PARTED ? c1 : fma_(min_(w.s1, T(0)), w.a1, c1);
+    const T e2 = fma_(PARTED ? w.s2 : min_(w.s2, T(0)), w.a2, c2);
     const T e3 = fma_(min_(w.s3, T(0)), w.a3, c3);
     const T g1 = fma_(w.s1, w.a1, -e1);
     const T g2 = fma_(w.s2, w.a2, -e2);
@@ -632,19 +652,32 @@ __device__ __forceinline__ Cell<T> x1_sweep(const Cell<T>& q, T dt, T beta, T hr
     const T uL = from_lo(u), vL = from_lo(v);
     Wave<T> w;
     T D;
-    const T spd = roe_sh(RL, ML, NL, uL, vL, q.R, q.M, q.N, u, v, beta, Sr, h, w, D);
-    if constexpr (COUNT) acc.add(spd, D);
-    // waves of the interface to the right -> products with it; the lane
-    // to the left supplies the products with the interface below
-    Wave<T> wr;
-    wr.a1 = from_hi(w.a1); wr.s1 = from_hi(w.s1); wr.r1 = from_hi(w.r1);
-    wr.a2 = from_hi(w.a2); wr.s2 = from_hi(w.s2); wr.r2 = from_hi(w.r2);
-    wr.a3 = from_hi(w.a3);
-    T tup[3], dhi[3], dlo[3];
-    wave_cross(w, wr, tup, dhi);
-    dlo[0] = from_lo(tup[0]); dlo[1] = from_lo(tup[1]); dlo[2] = from_lo(tup[2]);
-    T Gm[3], Gp[3];
-    hr_split(w, dlo, dhi, dt, Gm, Gp);
+    bool parted;
+    const T spd = roe_sh(RL, ML, NL, uL, vL, q.R, q.M, q.N, u, v, beta, Sr, h, w, D, parted);
+    T dhi[3], dlo[3], Gm[3], Gp[3];
+    if (__builtin_expect(all_lanes(parted), 1)) {
+        if constexpr (COUNT) acc.add(spd);
+        // family 1 meets the interface to the left, family 2 the one to the right
+        const T x1 = fma_(from_lo(w.r1), w.r1, fma_(from_lo(w.s1), w.s1, T(1)));
+        const T x2 = fma_(w.r2, from_hi(w.r2), fma_(w.s2, from_hi(w.s2), T(1)));
+        dlo[0] = from_lo(w.a1) * x1;
+        dhi[1] = from_hi(w.a2) * x2;
+        dlo[2] = from_lo(w.a3);
+        dhi[2] = from_hi(w.a3);
+        hr_split<true>(w, dlo, dhi, dt, Gm, Gp);
+    } else {
+        if constexpr (COUNT) acc.add(spd, D);
+        // waves of the interface to the right -> products with it; the lane
+        // to the left supplies the products with the interface below
+        Wave<T> wr;
+        wr.a1 = from_hi(w.a1); wr.s1 = from_hi(w.s1); wr.r1 = from_hi(w.r1);
+        wr.a2 = from_hi(w.a2); wr.s2 = from_hi(w.s2); wr.r2 = from_hi(w.r2);
+        wr.a3 = from_hi(w.a3);
+        T tup[3];
+        wave_cross(w, wr, tup, dhi);
+        dlo[0] = from_lo(tup[0]); dlo[1] = from_lo(tup[1]); dlo[2] = from_lo(tup[2]);
+        hr_split<false>(w, dlo, dhi, dt, Gm, Gp);
+    }
     const T g0 = from_hi(Gm[0]), g1 = from_hi(Gm[1]), g2 = from_hi(Gm[2]);
     Cell<T> o;
     o.R = fma_(-dt, g0 + Gp[0], q.R);
@@ -1039,6 +1072,7 @@ __device__ __forceinline__ void source_row(const SimDesc& d, int j, T k, const C
 template <typename T> struct Carry {
     Cell<T> q; T u, v;      // last x1-swept row Q*_v pushed, and its velocities
     Wave<T> w;              // x2 interface v - 1/2
+    bool parted;            // hr_split's PARTED holds there in every lane
     T dlo[3];               // upwind values t of x2 interface v-3/2 for v-1/2 (wave_cross)
     Cell<T> part;           // Q*_{v-1} - dt Gp_{v-3/2}: row v-1 awaiting its upper flux
     Cell<T> qs; T us, vs;   // x2-swept row v-2 awaiting its source, and its velocities
@@ -1051,6 +1085,7 @@ __device__ __forceinline__ void carry_zero(Carry<T>& c)
     const T z = T(0);
     c.q = {z, z, z}; c.u = z; c.v = z;
     c.w = {z, z, z, z, z, z, z, z};
+    c.parted = false;
     c.dlo[0] = c.dlo[1] = c.dlo[2] = z;
     c.part = {z, z, z};
     c.qs = {z, z, z}; c.us = z; c.vs = z;
@@ -1213,13 +1248,19 @@ __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, cons
         // x2 interface v-1/2 between rows v-1 (low) and v (high); normal = N
         Wave<T> wA;
         T D;
-        const T spd = roe_sh(in.q.R, in.q.N, in.q.M, in.v, in.u, q.R, q.N, q.M, vv, u, beta, Sr, h, wA, D);
-        if (LEAN || (v > vfirst && (pery || (v >= 0 && v <= ny)))) yacc.add(spd, D);
+        bool parted;
+        const T spd = roe_sh(in.q.R, in.q.N, in.q.M, in.v, in.u, q.R, q.N, q.M, vv, u, beta, Sr, h, wA, D, parted);
+        out.parted = all_lanes(parted);
+        if (LEAN || (v > vfirst && (pery || (v >= 0 && v <= ny)))) {
+            if (__builtin_expect(out.parted, 1)) yacc.add(spd);
+            else yacc.add(spd, D);
+        }
         T tup[3], dhi[3];
         wave_cross(in.w, wA, tup, dhi);
         // limited correction and fluctuations at v-3/2
         T Gm[3], Gp[3];
-        hr_split(in.w, in.dlo, dhi, dt, Gm, Gp);
+        if (__builtin_expect(in.parted, 1)) hr_split<true>(in.w, in.dlo, dhi, dt, Gm, Gp);
+        else hr_split<false>(in.w, in.dlo, dhi, dt, Gm, Gp);
         // row v-2 completes; row v-1 receives its lower flux (split-local order R, N, M)
         Cell<T> qn;
         qn.R = fma_(-dt, Gm[0], in.part.R);
@@ -1596,7 +1637,8 @@ __device__ __forceinline__ void block_march(const SimDesc& d, int strip, int r0,
             rcp_pair(T(1) + ql.R, T(2) + (Rl2 + ql.R), irl, hl);
             const T u = q.M * ir, vv = q.N * ir, ul = ql.M * irl, vl = ql.N * irl;
             T D;
-            const T spd = roe_sh(ql.R, ql.N, ql.M, vl, ul, q.R, q.N, q.M, vv, u, beta, Sr, h, wB, D);
+            bool parted;
+            const T spd = roe_sh(ql.R, ql.N, ql.M, vl, ul, q.R, q.N, q.M, vv, u, beta, Sr, h, wB, D, parted);
             if (v > vfirst && (pery || (v >= 0 && v <= ny))) yacc.add(spd, D);
             sh.wave[0][i][lane] = wB.s1; sh.wave[1][i][lane] = wB.s2; sh.wave[2][i][lane] = wB.s3;
             sh.wave[3][i][lane] = wB.a1; sh.wave[4][i][lane] = wB.a2; sh.wave[5][i][lane] = wB.a3;
@@ -1617,11 +1659,16 @@ __device__ __forceinline__ void block_march(const SimDesc& d, int strip, int r0,
                 return Wave<T>{p[0], p[st], p[2 * st], p[3 * st], p[4 * st], p[5 * st], p[6 * st], p[7 * st]};
             };
             const Wave<T> wA = wave_at(1), wL = wave_at(2);
-            T dlo[3], dhi[3], t0[3], t1[3];
-            wave_cross(wL, wA, dlo, t0);
-            wave_cross(wA, wB, t1, dhi);
-            T Gp[3];
-            hr_split(wA, dlo, dhi, dt, Gm, Gp);
+            T dlo[3], dhi[3], t0[3], t1[3], Gp[3];
+            if (__builtin_expect(all_lanes(wA.s1 > T(0) && wA.s2 < T(0)), 1)) {
+                wave_cross(wL, wA, dlo, t0);           // what hr_split<true> leaves out of
+                wave_cross(wA, wB, t1, dhi);           // these is neither read nor formed
+                hr_split<true>(wA, dlo, dhi, dt, Gm, Gp);
+            } else {
+                wave_cross(wL, wA, dlo, t0);
+                wave_cross(wA, wB, t1, dhi);
+                hr_split<false>(wA, dlo, dhi, dt, Gm, Gp);
+            }
             part.R = fma_(-dt, Gp[0], ql.R);
             part.N = fma_(-dt, Gp[1], ql.N);
             part.M = fma_(-dt, Gp[2], ql.M);
