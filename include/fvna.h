@@ -27,6 +27,9 @@
  *   - Device memory is owned by the caller (e.g. PyTorch tensors): the
  *     library records the pointers it is given and never frees them.  Sizes
  *     come from fvna_workspace_size().  The HIP stream is borrowed.
+ *   - Answers (clock, sums, windows, states) come through pinned host memory
+ *     of the context: 0.2 MB pinned at the first one, 2 MB more at the first
+ *     of 4 MB, given back by destroy.
  *   - Every call returns an fvna_status; no C++ exception crosses the ABI.
  *     On failure fvna_last_error() returns a thread-local message.
  *   - Errors found on the device while stepping (non-real Roe speeds,

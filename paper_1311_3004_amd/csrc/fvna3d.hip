@@ -34,6 +34,7 @@
 
 #include "../../include/fvna3d.h"
 #include "fvna_device.hpp"
+#include "fvna_reply.hpp"
 #include "fvna_step.hpp"
 
 using namespace fvna;
@@ -691,15 +692,14 @@ __global__ void k3_import(Desc3 d, const double* __restrict__ src, int field, do
 }
 
 template <typename T>
-__global__ void k3_export(Desc3 d, double* __restrict__ dst, int field, double factor)
+__global__ void k3_export(Desc3 d, double* __restrict__ dst, int field, long long row0, long long nrows, double factor)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= d.n[0]) return;
-    const int rows = d.n[1] * d.n[2];
     const int cur = d.clk->cur;
     const T* base = (const T*)d.buf[field == 0 ? buf_rho(cur) : buf_mom(cur)] + (size_t)field * (size_t)d.plane;
-    for (int r = blockIdx.y; r < rows; r += gridDim.y)
-        dst[(size_t)r * d.n[0] + i] = (double)base[(size_t)r * (size_t)d.pitch + i] * factor;
+    for (long long r = blockIdx.y; r < nrows; r += gridDim.y)
+        dst[(size_t)r * d.n[0] + i] = (double)base[(size_t)(row0 + r) * (size_t)d.pitch + i] * factor;
 }
 
 thread_local std::string g_err3 = "no error";
@@ -788,6 +788,7 @@ struct fvna3_ctx {
     char* scratch;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
+    Reply reply;
     void (*attempt)(const Desc3&, int force, int pos, long long owed, hipStream_t) = nullptr;
 };
 
@@ -846,8 +847,7 @@ fvna_status enqueue3(fvna3_ctx* c, long long attempts, long long owed = 0)
 
 fvna_status read_clock3(fvna3_ctx* c, Clock* h)
 {
-    HIP3(hipStreamSynchronize(c->s));
-    HIP3(hipMemcpy(h, c->d.clk, sizeof(Clock), hipMemcpyDeviceToHost));
+    HIP3(read_words(c->reply, c->s, c->d.clk, h, sizeof(Clock)));
     return FVNA_OK;
 }
 
@@ -1003,7 +1003,6 @@ fvna_status fvna3_set_state(fvna3_ctx* c, const double* rho_p, const double* m1,
         if (p.precision == FVNA_F64) hipLaunchKernelGGL(k3_import<double>, grid, dim3(256), 0, c->s, d, stage, f, denom[f]);
         else hipLaunchKernelGGL(k3_import<float>, grid, dim3(256), 0, c->s, d, stage, f, denom[f]);
         HIP3(hipGetLastError());
-        HIP3(hipStreamSynchronize(c->s));
     }
     const double dt0 = p.dt0 > 0 ? p.dt0 * p.c0 / p.dx : 0.0;
     hipLaunchKernelGGL(k3_clock, dim3(1), dim3(64), 0, c->s, d.clk, 0.0, dt0, 0);
@@ -1014,6 +1013,7 @@ fvna_status fvna3_set_state(fvna3_ctx* c, const double* rho_p, const double* m1,
         hipLaunchKernelGGL(k3_dt0, dim3(1), dim3(64), 0, c->s, d);
         HIP3(hipGetLastError());
     }
+    // waits for the stream: the caller's arrays are free when this returns
     Clock h;
     fvna_status s = read_clock3(c, &h);
     if (s) return s;
@@ -1044,11 +1044,21 @@ fvna_status fvna3_get_state(fvna3_ctx* c, double* rho_p, double* m1, double* m2,
     const double fac[4] = {p.rho0, p.rho0 * p.c0, p.rho0 * p.c0, p.rho0 * p.c0};
     const size_t n = (size_t)p.nx * p.ny * p.nz;
     double* stage = (double*)(c->scratch + OFF3_STAGE);
+    const long long rows = (long long)p.ny * p.nz;
+    auto fill = [&](int f, long long r0, long long nr, double* out) {
+        const dim3 grid((p.nx + 255) / 256, (unsigned)std::min(nr, 65535ll));
+        if (p.precision == FVNA_F64)
+            hipLaunchKernelGGL(k3_export<double>, grid, dim3(256), 0, c->s, d, out, f, r0, nr, fac[f]);
+        else hipLaunchKernelGGL(k3_export<float>, grid, dim3(256), 0, c->s, d, out, f, r0, nr, fac[f]);
+    };
+    hipError_t err;
+    if (stream_out(c->reply, c->s, 4, rows, p.nx, stage, dst, fill, err)) {
+        HIP3(err);
+        return FVNA_OK;
+    }
     HIP3(hipStreamSynchronize(c->s));
-    const dim3 grid((p.nx + 255) / 256, std::min(p.ny * p.nz, 65535));
     for (int f = 0; f < 4; ++f) {
-        if (p.precision == FVNA_F64) hipLaunchKernelGGL(k3_export<double>, grid, dim3(256), 0, c->s, d, stage, f, fac[f]);
-        else hipLaunchKernelGGL(k3_export<float>, grid, dim3(256), 0, c->s, d, stage, f, fac[f]);
+        fill(f, 0, rows, stage);
         HIP3(hipGetLastError());
         HIP3(hipMemcpyAsync(dst[f], stage, n * sizeof(double), hipMemcpyDeviceToHost, c->s));
         HIP3(hipStreamSynchronize(c->s));

@@ -15,6 +15,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -23,6 +24,7 @@
 
 #include "../../include/fvna.h"
 #include "fvna_device.hpp"
+#include "fvna_reply.hpp"
 #include "fvna_step.hpp"
 
 using namespace fvna;
@@ -301,6 +303,30 @@ __global__ void k_export(SimDesc d, double* __restrict__ dst, int field, int row
     if (i >= ncols || r >= nrows) return;
     const S* src = (const S*)d.buf[d.clk->cur] + (size_t)field * d.plane + (size_t)(row0 + r) * d.pitch + col0;
     dst[(size_t)r * ncols + i] = (double)Codec<S, T>::ld(src[i], d.scale[field]) * factor;
+}
+
+// k_export of all three fields of a small window, field f to dst + f stride.
+template <typename S, typename T>
+__global__ void k_export3(SimDesc d, double* __restrict__ dst, int stride, int row0, int col0, int ncols, double f0,
+                          double f12)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, r = blockIdx.y, f = blockIdx.z;
+    if (i >= ncols) return;
+    const S* src = (const S*)d.buf[d.clk->cur] + (size_t)f * d.plane + (size_t)(row0 + r) * d.pitch + col0;
+    dst[(size_t)f * stride + (size_t)r * ncols + i] = (double)Codec<S, T>::ld(src[i], d.scale[f]) * (f == 0 ? f0 : f12);
+}
+
+// The clocks of a batch, one block each.
+__global__ void k_batch_clocks(const SimDesc* __restrict__ descs, Clock* __restrict__ dst)
+{
+    const unsigned long long* src = (const unsigned long long*)descs[blockIdx.x].clk;
+    unsigned long long* o = (unsigned long long*)(dst + blockIdx.x);
+    for (int k = threadIdx.x; k < (int)(sizeof(Clock) / 8); k += blockDim.x) o[k] = src[k];
+}
+
+__global__ void k_set_clock(Clock* c, Clock h)
+{
+    if (threadIdx.x == 0) *c = h;
 }
 
 // Moving domain (Sec. 4): the state moved WinState::move cells along +x1 into
@@ -758,6 +784,7 @@ struct Launcher {
     void (*dry)(const SimDesc&, hipStream_t);
     void (*imp)(const SimDesc&, const double*, int, int, int, double, int, hipStream_t);
     void (*exp)(const SimDesc&, double*, int, int, int, int, int, double, hipStream_t);
+    void (*exp3)(const SimDesc&, double*, int, int, int, int, int, double, double, hipStream_t);
     void (*sums)(const SimDesc&, const void* state, double* part, double* out, const double* factor, hipStream_t);
     void (*shift)(const SimDesc&, hipStream_t);
     void (*close)(const SimDesc&, const RecDesc&, int last, long long owed, const WinRule&, hipStream_t);
@@ -797,6 +824,11 @@ Launcher make_launcher()
                hipStream_t s) {
         hipLaunchKernelGGL((k_export<S, T>), dim3((ncols + 255) / 256, nrows), dim3(256), 0, s, d, dst, field, row0,
                            nrows, col0, ncols, factor);
+    };
+    L.exp3 = [](const SimDesc& d, double* dst, int stride, int row0, int nrows, int col0, int ncols, double f0,
+                double f12, hipStream_t s) {
+        hipLaunchKernelGGL((k_export3<S, T>), dim3((ncols + 255) / 256, nrows, 3), dim3(256), 0, s, d, dst, stride, row0,
+                           col0, ncols, f0, f12);
     };
     L.sums = [](const SimDesc& d, const void* state, double* part, double* out, const double* factor,
                 hipStream_t s) {
@@ -873,6 +905,8 @@ struct fvna_ctx {
     RecDesc rec{};              // rec.on: a recorder follows every attempt
     bool taylor = false;        // fvna_set_taylor was called
     double ta_amp_pa = 0.0, ta_x0_m = 0.0;
+    std::unique_ptr<Reply> own;
+    Reply* reply = nullptr;     // own, or the batch's of which this is a member
 };
 
 // n attempts in a row on stream s: attempts after the first take the decision
@@ -913,12 +947,14 @@ static fvna_status build_graph(fvna_ctx* c)
 }
 
 // Host copy of the clock.
-static fvna_status read_clock(fvna_ctx* c, Clock* h)
+// The first `bytes` of the clock area (Clock, ClockAux, WinState), once
+// everything enqueued before is done.
+static fvna_status read_area(fvna_ctx* c, void* h, size_t bytes)
 {
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    HIP_TRY(hipMemcpy(h, c->clk, sizeof(Clock), hipMemcpyDeviceToHost));
+    HIP_TRY(read_words(*c->reply, c->stream, c->clk, h, bytes));
     return FVNA_OK;
 }
+static fvna_status read_clock(fvna_ctx* c, Clock* h) { return read_area(c, h, sizeof(Clock)); }
 
 static fvna_status status_of(int st)
 {
@@ -941,8 +977,8 @@ static fvna_status reset_clock(fvna_ctx* c, double t_dimless, double dt_dimless,
     h.dt = dt_dimless > 0.0 ? dt_dimless : 0.0;
     h.cur = cur;
     h.x_off = x_off;
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    HIP_TRY(hipMemcpy(c->clk, &h, sizeof(Clock), hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(k_set_clock, dim3(1), dim3(64), 0, c->stream, c->clk, h);
+    HIP_TRY(hipGetLastError());
     if (c->rec.on) {
         // the step count restarts at 0: the recorder counts from here on
         // (its descriptor is a kernel argument of the captured graph)
@@ -954,8 +990,8 @@ static fvna_status reset_clock(fvna_ctx* c, double t_dimless, double dt_dimless,
         HIP_TRY(hipGetLastError());
         hipLaunchKernelGGL(k_dt0, dim3(1), dim3(64), 0, c->stream, c->d);
         HIP_TRY(hipGetLastError());
-        HIP_TRY(hipStreamSynchronize(c->stream));
     }
+    HIP_TRY(hipStreamSynchronize(c->stream));
     return FVNA_OK;
 }
 
@@ -982,7 +1018,12 @@ fvna_status fvna_create(const fvna_params* p, void* state_a, void* state_b, void
         return fail(FVNA_E_INVALID, "device buffers must be 256-byte aligned");
     if (state_a == state_b) return fail(FVNA_E_INVALID, "state_a and state_b must differ");
     fvna_ctx* c = new (std::nothrow) fvna_ctx();
-    if (!c) return fail(FVNA_E_NOMEM, "out of host memory");
+    if (c) c->own.reset(new (std::nothrow) Reply);
+    if (!c || !c->own) {
+        delete c;
+        return fail(FVNA_E_NOMEM, "out of host memory");
+    }
+    c->reply = c->own.get();
     c->p = *p;
     c->stream = (hipStream_t)hip_stream;
     c->scratch = (char*)scratch;
@@ -1122,8 +1163,8 @@ fvna_status fvna_set_state(fvna_ctx* c, const double* rho_p, const double* mom_x
                                    hipMemcpyHostToDevice, c->stream));
             c->L.imp(c->d, stage, f, (int)r0, (int)nr, denom[f], 0, c->stream);
             HIP_TRY(hipGetLastError());
-            HIP_TRY(hipStreamSynchronize(c->stream));
         }
+    // waits for the stream: the caller's arrays are free when this returns
     return reset_clock(c, 0.0, p.dt0 > 0 ? p.dt0 * p.c0 / p.dx : 0.0, 0);
 }
 
@@ -1163,19 +1204,30 @@ fvna_status fvna_step(fvna_ctx* c, int64_t nsteps)
     return enqueue_attempts(c, nsteps);
 }
 
+// Complete the steps owed.  ask() launches what forms an answer into the reply;
+// it comes with the clock that says whether it is the settled state's, and is
+// asked for again if not.
+extern "C++" template <typename Ask>
+static fvna_status settle(fvna_ctx* c, Clock* h, Ask&& ask)
+{
+    for (int guard = 0; guard < 1000; ++guard) {
+        ask();
+        HIP_TRY(hipGetLastError());
+        fvna_status s = read_clock(c, h);
+        if (s) return s;
+        if (h->status != 0 || h->accepted >= h->target) return status_of(h->status);
+        // rejected attempts left steps owed: run more attempts
+        s = enqueue_attempts(c, h->target - h->accepted);
+        if (s) return s;
+    }
+    return fail(FVNA_E_STATE, "steps still owed after many top-up rounds");
+}
+
 fvna_status fvna_sync(fvna_ctx* c)
 {
     if (!c) return fail(FVNA_E_INVALID, "ctx is NULL");
     Clock h;
-    for (int guard = 0; guard < 1000; ++guard) {
-        fvna_status s = read_clock(c, &h);
-        if (s) return s;
-        if (h.status != 0 || h.accepted >= h.target) return status_of(h.status);
-        // rejected attempts left steps owed: run more attempts
-        s = enqueue_attempts(c, h.target - h.accepted);
-        if (s) return s;
-    }
-    return fail(FVNA_E_STATE, "steps still owed after many top-up rounds");
+    return settle(c, &h, [] {});
 }
 
 fvna_status fvna_set_recorder(fvna_ctx* c, const fvna_recorder* r)
@@ -1275,8 +1327,9 @@ fvna_status fvna_step_window(fvna_ctx* c, const fvna_window* w, fvna_window_stat
             phase = (phase + k) % w->check_every;
         }
         struct { Clock clk; char gap[WIN_OFFSET - sizeof(Clock)]; WinState win; } h;
-        HIP_TRY(hipStreamSynchronize(c->stream));
-        HIP_TRY(hipMemcpy(&h, c->clk, sizeof(h), hipMemcpyDeviceToHost));
+        static_assert(sizeof(h) <= REPLY_HEAD && sizeof(h) % 8 == 0, "the clock area is read in words");
+        const fvna_status rd = read_area(c, &h, sizeof(h));
+        if (rd) return rd;
         st->x_off = h.win.x_off;
         st->phase = h.win.phase;
         if (h.win.halted) return fail(FVNA_E_INVALID, "moving-domain jump too large");
@@ -1298,6 +1351,13 @@ static fvna_status export_window(fvna_ctx* c, int i0, int j0, int ni, int nj, do
     const size_t chunk_rows = std::max<size_t>(1, stage_cells_of(&p) / (size_t)ni);
     const double factor[3] = {p.rho0, p.rho0 * p.c0, p.rho0 * p.c0};
     double* dst[3] = {rho_p, mom_x, mom_y};
+    hipError_t err;
+    if (stream_out(*c->reply, c->stream, 3, nj, ni, stage, dst, [&](int f, long long r0, long long nr, double* out) {
+            c->L.exp(c->d, out, f, (int)(j0 + r0), (int)nr, i0, ni, factor[f], c->stream);
+        }, err)) {
+        HIP_TRY(err);
+        return FVNA_OK;
+    }
     HIP_TRY(hipStreamSynchronize(c->stream));
     for (int f = 0; f < 3; ++f)
         for (size_t r0 = 0; r0 < (size_t)nj; r0 += chunk_rows) {
@@ -1330,24 +1390,6 @@ static void stats_from_clock(const Clock& h, const fvna_params& p, fvna_stats* s
     st->status_step = h.status_step;
 }
 
-static fvna_status stats_of(fvna_ctx* c, fvna_stats* st)
-{
-    Clock h;
-    fvna_status r = read_clock(c, &h);
-    if (r) return r;
-    const double tu = c->p.dx / c->p.c0;
-    st->t = h.t * tu;
-    st->dt_next = h.dt * tu;
-    st->nu_last = h.nu_last;
-    st->nu_mean = h.nu_mean;
-    st->nu_std = h.nu_count > 0 ? std::sqrt(h.nu_m2 / (double)h.nu_count) : 0.0;
-    st->steps = h.accepted;
-    st->rejected = h.rejected;
-    st->status = h.status;
-    st->status_step = h.status_step;
-    return FVNA_OK;
-}
-
 static bool is_device_error(fvna_status s)
 {
     return s == FVNA_E_NONHYPERBOLIC || s == FVNA_E_NONFINITE || s == FVNA_E_RETRIES;
@@ -1355,14 +1397,8 @@ static bool is_device_error(fvna_status s)
 
 fvna_status fvna_get_state(fvna_ctx* c, double* rho_p, double* mom_x, double* mom_y)
 {
-    if (!c || !rho_p || !mom_x || !mom_y) return fail(FVNA_E_INVALID, "NULL argument");
-    const fvna_status dev = fvna_sync(c);
-    if (dev != FVNA_OK && !is_device_error(dev)) return dev;
-    const std::string msg = g_err;
-    fvna_status s = export_state(c, rho_p, mom_x, mom_y);
-    if (s) return s;
-    if (dev != FVNA_OK) g_err = msg;
-    return dev;
+    if (!c) return fail(FVNA_E_INVALID, "NULL argument");
+    return fvna_get_window(c, 0, 0, c->p.nx, c->p.ny, rho_p, mom_x, mom_y);
 }
 
 fvna_status fvna_get_window(fvna_ctx* c, int32_t i0, int32_t j0, int32_t ni, int32_t nj, double* rho_p,
@@ -1371,8 +1407,19 @@ fvna_status fvna_get_window(fvna_ctx* c, int32_t i0, int32_t j0, int32_t ni, int
     if (!c || !rho_p || !mom_x || !mom_y) return fail(FVNA_E_INVALID, "NULL argument");
     if (ni < 1 || nj < 1 || i0 < 0 || j0 < 0 || (long long)i0 + ni > c->p.nx || (long long)j0 + nj > c->p.ny)
         return fail(FVNA_E_INVALID, "window outside the grid");
-    const fvna_status dev = fvna_sync(c);
+    Clock h;
+    std::lock_guard<std::recursive_mutex> lock(c->reply->mu);
+    double* dst = (long long)ni * nj <= REPLY_CELLS ? c->reply->cells() : nullptr;
+    const int n = dst ? ni * nj : 0;
+    const fvna_status dev = settle(c, &h, [&] {
+        if (dst) c->L.exp3(c->d, dst, n, j0, nj, i0, ni, c->p.rho0, c->p.rho0 * c->p.c0, c->stream);
+    });
     if (dev != FVNA_OK && !is_device_error(dev)) return dev;
+    if (dst) {
+        double* out[3] = {rho_p, mom_x, mom_y};
+        for (int f = 0; f < 3; ++f) std::memcpy(out[f], dst + (size_t)f * n, (size_t)n * sizeof(double));
+        return dev;
+    }
     const std::string msg = g_err;
     fvna_status s = export_window(c, i0, j0, ni, nj, rho_p, mom_x, mom_y);
     if (s) return s;
@@ -1383,27 +1430,26 @@ fvna_status fvna_get_window(fvna_ctx* c, int32_t i0, int32_t j0, int32_t ni, int
 fvna_status fvna_get_stats(fvna_ctx* c, fvna_stats* st)
 {
     if (!c || !st) return fail(FVNA_E_INVALID, "NULL argument");
-    const fvna_status dev = fvna_sync(c);
+    Clock h;
+    const fvna_status dev = settle(c, &h, [] {});
     if (dev != FVNA_OK && !is_device_error(dev)) return dev;
-    const std::string msg = g_err;
-    fvna_status s = stats_of(c, st);
-    if (s) return s;
-    if (dev != FVNA_OK) g_err = msg;
+    stats_from_clock(h, c->p, st);
     return dev;
 }
 
 fvna_status fvna_sums(fvna_ctx* c, double out[3])
 {
     if (!c || !out) return fail(FVNA_E_INVALID, "NULL argument");
-    fvna_status s = fvna_sync(c);
-    if (s != FVNA_OK && !is_device_error(s)) return s;
     double* part = (double*)(c->scratch + OFF_PART);
-    double* res = (double*)(c->scratch + OFF_SUMOUT);
+    std::lock_guard<std::recursive_mutex> lock(c->reply->mu);
+    double* pin = c->reply->cells();
+    double* res = pin ? pin : (double*)(c->scratch + OFF_SUMOUT);
     const double factor[3] = {c->p.rho0, c->p.rho0 * c->p.c0, c->p.rho0 * c->p.c0};
-    c->L.sums(c->d, nullptr, part, res, factor, c->stream);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    HIP_TRY(hipMemcpy(out, res, 3 * sizeof(double), hipMemcpyDeviceToHost));
+    Clock h;
+    const fvna_status s = settle(c, &h, [&] { c->L.sums(c->d, nullptr, part, res, factor, c->stream); });
+    if (s != FVNA_OK && !is_device_error(s)) return s;
+    if (pin) std::memcpy(out, pin, 3 * sizeof(double));
+    else HIP_TRY(hipMemcpy(out, res, 3 * sizeof(double), hipMemcpyDeviceToHost));
     return FVNA_OK;
 }
 
@@ -1414,11 +1460,9 @@ fvna_status fvna_taylor_errors(fvna_ctx* c, double front0_x_m, double front0_y_m
     if (!c->taylor) return fail(FVNA_E_INVALID, "no Taylor profile set (fvna_set_taylor)");
     if (!(half_length_m > 0.0) || !std::isfinite(front0_x_m) || !std::isfinite(front0_y_m))
         return fail(FVNA_E_INVALID, "need a positive half length and a finite front point");
-    fvna_status s = fvna_sync(c);
-    if (s != FVNA_OK && !is_device_error(s)) return s;
     Clock h;
-    s = read_clock(c, &h);
-    if (s) return s;
+    fvna_status s = settle(c, &h, [] {});
+    if (s != FVNA_OK && !is_device_error(s)) return s;
     const fvna_params& p = c->p;
     ErrLine L;
     L.c = c->d.ta_cos;
@@ -1440,11 +1484,14 @@ fvna_status fvna_taylor_errors(fvna_ctx* c, double front0_x_m, double front0_y_m
         return fail(FVNA_E_INVALID, "the line has no cells");
     L.a0 = (long long)lo;
     L.n = (long long)hi - (long long)lo + 1;
-    double* res = (double*)(c->scratch + OFF_SUMOUT);
+    std::lock_guard<std::recursive_mutex> lock(c->reply->mu);
+    double* pin = c->reply->cells();
+    double* res = pin ? pin : (double*)(c->scratch + OFF_SUMOUT);
     c->L.taylor_err(c->d, L, res, c->stream);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(c->stream));
-    HIP_TRY(hipMemcpy(out, res, 2 * sizeof(double), hipMemcpyDeviceToHost));
+    if (pin) std::memcpy(out, pin, 2 * sizeof(double));
+    else HIP_TRY(hipMemcpy(out, res, 2 * sizeof(double), hipMemcpyDeviceToHost));
     if (!std::isfinite(out[0]) || !std::isfinite(out[1]))
         return fail(FVNA_E_INVALID, "no cell of the line lies in the domain");
     return FVNA_OK;
@@ -1592,6 +1639,7 @@ struct fvna_batch {
     hipStream_t cap;
     SimDesc* d_desc = nullptr;      // device copy of the descriptors
     TileRef* d_tiles = nullptr;
+    Reply reply;                    // its tail: the members' clocks
     int ntiles = 0;
     int tile_cap = 0;               // TileRefs d_tiles can hold
     hipGraphExec_t exec = nullptr;
@@ -1648,6 +1696,7 @@ static fvna_status batch_graph(fvna_batch* b)
 static fvna_ctx member_ctx(fvna_batch* b, int k)
 {
     fvna_ctx c;
+    c.reply = &b->reply;
     c.p = b->p[k];
     c.d = b->d[k];
     c.L = b->L;
@@ -1677,6 +1726,7 @@ fvna_status fvna_batch_create(int32_t n, const fvna_params* per_sim, void* const
     fvna_batch* b = new (std::nothrow) fvna_batch();
     if (!b) return fail(FVNA_E_NOMEM, "out of host memory");
     b->n = n;
+    b->reply.tail = (size_t)n * sizeof(Clock);
     b->stream = (hipStream_t)hip_stream;
     b->L = pick_launcher(per_sim[0].precision, per_sim[0].geometry);
     std::vector<int> tuned;
@@ -1779,29 +1829,28 @@ fvna_status fvna_batch_sync(fvna_batch* b)
 {
     if (!b) return fail(FVNA_E_INVALID, "batch is NULL");
     for (int guard = 0; guard < 1000; ++guard) {
+        std::unique_lock<std::recursive_mutex> lock(b->reply.mu);
+        const Clock* pin = (const Clock*)b->reply.end();
+        if (pin) {
+            hipLaunchKernelGGL(k_batch_clocks, dim3(b->n), dim3(64), 0, b->stream, b->d_desc, (Clock*)pin);
+            HIP_TRY(hipGetLastError());
+        }
         HIP_TRY(hipStreamSynchronize(b->stream));
         long long owed = 0;
         int worst = 0;
         for (int k = 0; k < b->n; ++k) {
             Clock h;
-            HIP_TRY(hipMemcpy(&h, b->scratch[k] + OFF_CLOCK, sizeof(Clock), hipMemcpyDeviceToHost));
+            if (pin) h = pin[k];
+            else HIP_TRY(hipMemcpy(&h, b->scratch[k] + OFF_CLOCK, sizeof(Clock), hipMemcpyDeviceToHost));
             if (h.status) worst = worst ? worst : h.status;
             else owed = std::max(owed, h.target - h.accepted);
         }
+        lock.unlock();
         if (owed <= 0) return status_of(worst);
         fvna_status s = batch_enqueue(b, owed);
         if (s) return s;
     }
     return fail(FVNA_E_STATE, "steps still owed after many top-up rounds");
-}
-
-// Device status of one member, as a status code (message set).
-static fvna_status member_status(fvna_ctx* c)
-{
-    Clock h;
-    fvna_status r = read_clock(c, &h);
-    if (r) return r;
-    return status_of(h.status);
 }
 
 fvna_status fvna_batch_get_state(fvna_batch* b, int32_t k, double* rho_p, double* mom_x, double* mom_y)
@@ -1810,7 +1859,10 @@ fvna_status fvna_batch_get_state(fvna_batch* b, int32_t k, double* rho_p, double
     const fvna_status bs = fvna_batch_sync(b);
     if (bs != FVNA_OK && !is_device_error(bs)) return bs;
     fvna_ctx c = member_ctx(b, k);
-    const fvna_status dev = member_status(&c);
+    Clock h;
+    const fvna_status rd = read_clock(&c, &h);
+    if (rd) return rd;
+    const fvna_status dev = status_of(h.status);
     if (dev != FVNA_OK && !is_device_error(dev)) return dev;
     const std::string msg = g_err;
     fvna_status s = export_state(&c, rho_p, mom_x, mom_y);
@@ -1825,12 +1877,12 @@ fvna_status fvna_batch_get_stats(fvna_batch* b, int32_t k, fvna_stats* st)
     const fvna_status bs = fvna_batch_sync(b);
     if (bs != FVNA_OK && !is_device_error(bs)) return bs;
     fvna_ctx c = member_ctx(b, k);
-    const fvna_status dev = member_status(&c);
+    Clock h;
+    const fvna_status rd = read_clock(&c, &h);
+    if (rd) return rd;
+    const fvna_status dev = status_of(h.status);
     if (dev != FVNA_OK && !is_device_error(dev)) return dev;
-    const std::string msg = g_err;
-    fvna_status s = stats_of(&c, st);
-    if (s) return s;
-    if (dev != FVNA_OK) g_err = msg;
+    stats_from_clock(h, c.p, st);
     return dev;
 }
 
