@@ -344,8 +344,39 @@ __device__ __forceinline__ void sweep12_lanes(const Desc3& d, int tile, int& seg
     col = c0 - HALO12 + loc;
 }
 
+// The wavefronts of a block raise as one: each leaves its values in LDS and the
+// last to come raises the attempt's (no barrier: they end when they end).  The
+// wavefronts of a launch whose tiles are all equally tall end together, read the
+// word before any has raised it, and wait for one another's atomics after all.
+// us per step with each for itself / by blocks: 224 x 100 x 40 FP32 in
+// 10-row tiles 54.6 / 45.0 (11-row tiles, the last of a plane shorter: 45.6 /
+// 45.7), 128^3 FP32 in 8-row tiles 78.1 / 65.2, 90 x 75 x 64 FP64 in 5-row tiles
+// 48.1 / 41.0.  (Not for the two-dimensional march, whose first and last segments
+// end early: 1319 x 813 FP64 39.1 / 40.5, 4096^2 level.)
+struct BlockCfl { unsigned long long smax; unsigned int flags, left; };
+
+// By every thread of the block, before its wavefronts part; n of them will raise.
+__device__ __forceinline__ void block_cfl_init(BlockCfl& b, int n)
+{
+    if (threadIdx.x == 0) { b.smax = 0ull; b.flags = 0u; b.left = (unsigned)n; }
+    __syncthreads();
+}
+
+__device__ __forceinline__ void cfl_raise_block(const Attempt& at, BlockCfl& b, double speed, bool nonhyp, bool nonfin)
+{
+    atomicMax(&b.smax, (unsigned long long)__double_as_longlong(speed));
+    const unsigned fl = (nonhyp ? FLAG_NONHYP : 0u) | (nonfin ? FLAG_NONFINITE : 0u);
+    if (fl) atomicOr(&b.flags, fl);
+    __threadfence_block();
+    if (atomicSub(&b.left, 1u) != 1u) return;
+    __threadfence_block();
+    const unsigned all = atomicOr(&b.flags, 0u);
+    cfl_raise(at, __longlong_as_double((long long)atomicMax(&b.smax, 0ull)), (all & FLAG_NONHYP) != 0,
+              (all & FLAG_NONFINITE) != 0);
+}
+
 template <typename T>
-__device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Attempt& at)
+__device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Attempt& at, BlockCfl& cfl)
 {
     const int nx = d.n[0], ny = d.n[1];
     const int lane = threadIdx.x & (WAVE - 1);
@@ -482,7 +513,7 @@ __device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Att
     T m = max_(sx, sy);
     for (int off = 32; off >= 1; off >>= 1) m = max_(m, perm(m, lane ^ off));
     const bool anyh = __any(hx || hy), anyf = __any(fx || fy);
-    if (lane == 0) cfl_raise(at, cfl_speed<T>(m), anyh, anyf);
+    if (lane == 0) cfl_raise_block(at, cfl, cfl_speed<T>(m), anyh, anyf);
 }
 
 template <typename T>
@@ -490,12 +521,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Occupancy<T
 void k3_sweep12(Desc3 d, int force, int pos, long long owed)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK + wave;
-    const int nfull = d.strips12 * d.segs12 * d.n[2];
-    if (tile >= nfull + d.tailk12 * d.segs12) return;
+    const int first = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK, tile = first + wave;
+    const int tiles = (d.strips12 * d.n[2] + d.tailk12) * d.segs12;
+    __shared__ BlockCfl cfl;
+    block_cfl_init(cfl, min(WAVES_PER_BLOCK, tiles - first));
+    if (tile >= tiles) return;
     pos = max(pos, 0);
     Attempt at;
-    if (step_begin(d, force, pos, owed, at)) sweep12_tile<T>(d, tile, at);
+    if (step_begin(d, force, pos, owed, at)) sweep12_tile<T>(d, tile, at, cfl);
     if (tile == 0 && (threadIdx.x & (WAVE - 1)) == 0) step_end(d, pos, owed);
 }
 
@@ -933,20 +966,27 @@ fvna_status fvna3_create(const fvna3_params* p, void* buf_a, void* buf_b, void* 
     // wavefronts let the dispatcher even out the load of the SIMDs, where
     // one round leaves some with a wavefront more than others (256^3, per
     // step: FP32 325 us with 43-row tiles, 333 with 64, 345 with 86, 371 with
-    // 128; 332 with 25).  A grid too small for that at 16 rows takes the rows
-    // of least (rows + 4 warm-up rows) x (1 with one wavefront per SIMD, 1.6
-    // with two, in proportion beyond), at least 4 (64^3 FP32: 6 rows 32.2 us per
-    // step, 16 rows 39.5, 4 rows 43.4; 90 x 75 x 64 FP64: 10 rows 42.0, 16 46.7).
+    // 128; 332 with 25).  A grid too small for that at 16 rows has all its tiles
+    // resident at once, and the CU with the most blocks (of four tiles) ends
+    // the sweep: m blocks on it take a row 1, 1.55, 2.15, ... = 0.35 + 0.6 m times
+    // as long as one (128^3 FP32: 0.93 us with one, 1.37, 1.88, 2.42, 2.93), and
+    // the height of least (rows + 4 warm-up rows) x that is taken, at least 4.
+    // us per step, by the total of tiles before / by blocks: 128^3 FP32 70 / 62
+    // (16 / 19 rows), FP64 103 / 90, 180 x 160 x 140 FP32 106 / 93 (32 / 24),
+    // 90 x 75 x 64 FP64 43 / 41 (10 / 5).
     {
         const long long units = (long long)d.strips12 * p->nz + d.tailk12;
         const long long simds = 4ll * cus, want = 6 * simds;
         const long long nseg = std::max(1ll, (want + units - 1) / units);
         long long rows = (p->ny + nseg - 1) / nseg;
         if (rows < 16) {
+            const int resident = p->precision == FVNA_F64 ? 3 : 5;         // blocks of k3_sweep12 on a CU
             double best = 1e30;
             for (long long r = std::min(4, p->ny); r <= p->ny; ++r) {
-                const double w = (double)(units * ((p->ny + r - 1) / r)) / (double)simds;
-                const double cost = (double)(r + 2 * HALO12) * (w <= 1.0 ? 1.0 : w <= 2.0 ? 1.6 : 0.8 * w);
+                const long long blocks = (units * ((p->ny + r - 1) / r) + 3) / 4, most = (blocks + cus - 1) / cus;
+                // past what is resident, blocks start as others end
+                const double m = most <= resident ? (double)most : (double)blocks / cus + 0.5;
+                const double cost = (double)(r + 2 * HALO12) * (most == 1 ? 1.0 : 0.35 + 0.6 * m);
                 if (cost < best) { best = cost; rows = r; }
             }
         }
