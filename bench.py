@@ -44,19 +44,19 @@ BYTES_PER_CELL = {"f64": 48, "f32": 24, "f32_f16store": 12, "f32_bf16store": 12}
 # after any change they report null until profiled again.
 PMC_SOURCES = ("csrc/fvna_device.hpp", "csrc/fvna_step.hpp", "csrc/fvna_runtime.hip", "build.py")
 _PROFILED = {
-    "csrc/fvna_device.hpp": "3e76f58f56c4e08409f419cb12c92d66809ea16bda2b4404b40fcf8540fd889c",
-    "csrc/fvna_step.hpp": "7cb19305ef45932c928fb8e9459319971a7cb3cf780226a7c8d87fc6e48d1620",
-    "csrc/fvna_runtime.hip": "ce718845ddf48abb486bc5463fe7bf7c4222ebac01bbf312b7c98bddc04e1b1f",
-    "build.py": "02eda4061ab4ab18fbd0c2e868524ec4e9acf39f5fa26d0513e48c2fca74259e",
+    "csrc/fvna_device.hpp": "e637fe5c80ade287be36e612881ab7192393a05623b41e5176b6762bf19de020",
+    "csrc/fvna_step.hpp": "d49f4a8d20130d8b4d1139716c8ae2c507493b313527b901fe85feef9b14fa96",
+    "csrc/fvna_runtime.hip": "eeaeacb8a80b16f18e24fa419059f010c4127f83fc229213f6019f3aeb7ba962",
+    "build.py": "0b96d334687a542c0a4c252f33e1b52c4a4d56c135c4ae89b01618e48ecc776c",
 }
 PMC = {
     # profiles/k_step_f64_gaussian4096.md
-    "k_step<double,double,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 4.1995e+08, "write_bytes": 4.0549e+08,
-                                "valu_lane_ops_per_cell": 400.6, "valu_issue_cycles_per_cell": 26.54,
+    "k_step<double,double,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 4.2302e+08, "write_bytes": 4.0447e+08,
+                                "valu_lane_ops_per_cell": 373.3, "valu_issue_cycles_per_cell": 24.84,
                                 "sources": _PROFILED},
     # profiles/k_step_f32_gaussian4096.md
-    "k_step<float,float,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 2.1448e+08, "write_bytes": 2.0345e+08,
-                              "valu_lane_ops_per_cell": 300.6, "valu_issue_cycles_per_cell": 19.74,
+    "k_step<float,float,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 2.1493e+08, "write_bytes": 2.0275e+08,
+                              "valu_lane_ops_per_cell": 287.9, "valu_issue_cycles_per_cell": 18.95,
                               "sources": _PROFILED},
 }
 

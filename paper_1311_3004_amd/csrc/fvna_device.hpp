@@ -1126,8 +1126,8 @@ struct Pace {
 //         overrides needed); interior strips compile without that logic.
 //   LEAN: every row the tile touches (three below the segment to three above)
 //         is a real row: no ghost rows, no periodic wrap, no boundary rows in
-//         the source, and the main loop has no branches at all.  Other
-//         segments take the general path.  Both paths evaluate every cell
+//         the source, and the main loop branches only on whether waves are
+//         parted (hr_split).  Other segments take the general path.  Both paths evaluate every cell
 //         with the same arithmetic, so results do not depend on the path.
 template <typename S, typename T, int AXI, bool EDGE, bool LEAN>
 __device__ __forceinline__ void march(const SimDesc& d, int strip, int seg, const Attempt& at)
@@ -1470,8 +1470,8 @@ __device__ __forceinline__ void march_tile(const SimDesc& d, int strip, int seg,
 //      v - 3/2, v - 1/2), lower flux into row v - 1       -> partial row
 //   D  row v - 2 completed, its velocities                -> x2-swept row
 //   E  source of row v - 3 (x2-swept rows v - 4 .. v - 2), store
-// so 16 rows take little longer than one, a SIMD always has four waves, and a
-// tall tile goes on with the next 16 rows: what its first rows need of the
+// so eight rows take little longer than one, two blocks share a CU (four waves a
+// SIMD), and a tall tile goes on with the next eight rows: what its first rows need of the
 // batch before (one cell, two interfaces, one partial row, two x2-swept rows)
 // is kept in LDS, and nothing is recomputed inside a tile.  A tile of n output
 // rows pushes rows r0 - 3 .. r1 + 2, n + 6 in all.
