@@ -228,6 +228,7 @@ __device__ __forceinline__ void march_push(const Q4<T>& q, const March4<T>& in, 
 {
     T ir, h;
     rcp_pair(T(1) + q.R, T(2) + (in.q.R + q.R), ir, h);
+    ir = rcp_polish(T(1) + q.R, ir);
     const T un = q.n * ir, ua = q.a * ir, ub = q.b * ir;
     W4<T> wA;
     T D;
@@ -418,6 +419,7 @@ __device__ __forceinline__ void sweep12_tile(const Desc3& d, int tile, const Att
         L.R = from_lo(q.R);
         T ir, h;
         rcp_pair(T(1) + q.R, T(2) + (L.R + q.R), ir, h);
+        ir = rcp_polish(T(1) + q.R, ir);           // the first lane's left cell is another plane's in a packed tail
         const T un = q.n * ir, ua = q.a * ir, ub = q.b * ir;
         L.n = from_lo(q.n); L.a = from_lo(q.a); L.b = from_lo(q.b);
         const T unL = from_lo(un), uaL = from_lo(ua), ubL = from_lo(ub);
