@@ -44,18 +44,18 @@ BYTES_PER_CELL = {"f64": 48, "f32": 24, "f32_f16store": 12, "f32_bf16store": 12}
 # after any change they report null until profiled again.
 PMC_SOURCES = ("csrc/fvna_device.hpp", "csrc/fvna_step.hpp", "csrc/fvna_runtime.hip", "build.py")
 _PROFILED = {
-    "csrc/fvna_device.hpp": "e637fe5c80ade287be36e612881ab7192393a05623b41e5176b6762bf19de020",
+    "csrc/fvna_device.hpp": "0fbf95b3c781188d7b080aab21983132e628c03b02a0d33e523ef15bedaabef9",
     "csrc/fvna_step.hpp": "d49f4a8d20130d8b4d1139716c8ae2c507493b313527b901fe85feef9b14fa96",
     "csrc/fvna_runtime.hip": "eeaeacb8a80b16f18e24fa419059f010c4127f83fc229213f6019f3aeb7ba962",
     "build.py": "0b96d334687a542c0a4c252f33e1b52c4a4d56c135c4ae89b01618e48ecc776c",
 }
 PMC = {
     # profiles/k_step_f64_gaussian4096.md
-    "k_step<double,double,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 4.2302e+08, "write_bytes": 4.0447e+08,
-                                "valu_lane_ops_per_cell": 373.3, "valu_issue_cycles_per_cell": 24.84,
+    "k_step<double,double,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 4.2271e+08, "write_bytes": 4.0461e+08,
+                                "valu_lane_ops_per_cell": 375.6, "valu_issue_cycles_per_cell": 24.99,
                                 "sources": _PROFILED},
     # profiles/k_step_f32_gaussian4096.md
-    "k_step<float,float,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 2.1493e+08, "write_bytes": 2.0275e+08,
+    "k_step<float,float,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 2.1489e+08, "write_bytes": 2.0268e+08,
                               "valu_lane_ops_per_cell": 287.9, "valu_issue_cycles_per_cell": 18.95,
                               "sources": _PROFILED},
 }
