@@ -337,9 +337,11 @@ fvna_status fvna_sums_noalloc(const fvna_params* p, const void* state, void* hip
  * simulation state and its results are unchanged. */
 fvna_status fvna_time_step_kernel(fvna_ctx* c, int32_t reps, double* ms_per_launch);
 
-/* Pick tile_rows for this context by timing each candidate with
- * fvna_time_step_kernel; writes the chosen value to *tile_rows.  Results are
- * bitwise independent of the choice. */
+/* Pick tile_rows for this context by timing the next step's attempt with each
+ * candidate, the plan in use and the library's default among them (state and
+ * clock are unchanged); writes the chosen value to *tile_rows.  Contexts created later in the process
+ * for the same precision, geometry, nx and ny with tile_rows 0 take the choice.
+ * Results are bitwise independent of it. */
 fvna_status fvna_autotune(fvna_ctx* c, int32_t* tile_rows);
 
 /* Rows per segment (or per block tile, on small grids) currently used by the

@@ -1,0 +1,78 @@
+"""The autotuners never leave a grid slower than it was: the plan in use and
+the default one are among what they time.  The grids are ones whose default
+tiles are far shorter than the listed heights (those took 1.6 to 2.3 times as
+long), so the margins are far above the scatter of the timings."""
+import time
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+MED = {"c0": 1500.0, "rho0": 1000.0, "beta": 3.5, "delta": 4.3e-6}
+
+
+def fields(nx, ny):
+    R = 1e-3 * np.random.default_rng(nx * ny).uniform(-1.0, 1.0, (ny, nx))
+    return 1000.0 * R, 4e5 * R, -3e5 * R
+
+
+def per_step(run):
+    """Seconds per step of run(steps), the best of several runs."""
+    run(40)
+    best = 1e30
+    for _ in range(7):
+        t = time.perf_counter()
+        run(40)
+        best = min(best, time.perf_counter() - t)
+    return best / 40
+
+
+def context(nx, ny, precision, tile_rows=0):
+    from paper_1311_3004_amd import fvna
+    s = fvna.Sim(fvna.make_params(nx, ny, 1e-4, MED, precision=precision, tile_rows=tile_rows))
+    s.fvna_set_state(*fields(nx, ny))
+    return s
+
+
+@pytest.mark.parametrize("nx,ny,precision,tile_rows", [(1000, 1000, "f32", 0), (720, 720, "f64", 0),
+                                                       (250, 260, "f64", 0), (730, 710, "f32", 128)])
+def test_autotuned_context_is_no_slower(nx, ny, precision, tile_rows):
+    """tile_rows 128: the caller's own height must not become the default of
+    later contexts.  State and clock are what they were."""
+    def step(s):
+        def run(n):
+            s.fvna_step(n)
+            s.fvna_sync()
+        return per_step(run)
+    a = context(nx, ny, precision)
+    before = step(a)
+    b = context(nx, ny, precision, tile_rows) if tile_rows else a
+    state, stats = b.fvna_get_state(), b.fvna_get_stats()
+    b.fvna_autotune()
+    assert b.fvna_get_stats() == stats
+    for x, y in zip(b.fvna_get_state(), state):
+        assert np.array_equal(x, y)
+    c = context(nx, ny, precision)
+    assert step(b) < 1.25 * before
+    assert step(c) < 1.25 * before
+    for s in (a, b, c):
+        s.fvna_destroy()
+
+
+def test_autotuning_between_steps_changes_no_result():
+    """Rejected and accepted attempts, FP64 and FP32, with tuning in between."""
+    from common import pulse_workload, run_gpu
+    w = pulse_workload(300, 260, ("extrap0", "reflect", "extrap0", "extrap0"))
+    dt0 = 1.3 * 0.9 * w["dx"] / w["medium"]["c0"]            # the first attempt is rejected
+    for precision in ("f64", "f32"):
+        a, sa, s = run_gpu(w, 40, precision, dt_si=dt0)
+        s.fvna_destroy()
+        b, sb, s = run_gpu(w, 0, precision, dt_si=dt0)
+        s.fvna_autotune()
+        s.fvna_step(13)
+        s.fvna_autotune()
+        b, sb, s = run_gpu(w, 27, precision, sim=s)
+        s.fvna_destroy()
+        assert sa["rejected"] >= 1 and sa == sb
+        for x, y in zip(a, b):
+            assert np.array_equal(x, y)
