@@ -374,9 +374,9 @@ fvna_status fvna_batch_get_stats(fvna_batch* b, int32_t k, fvna_stats* s);
 fvna_status fvna_batch_time_step_kernel(fvna_batch* b, int32_t reps, double* ms_per_launch);
 /* Choose the segment height of the members by timing the batched step kernel
  * on the batch itself: members are grouped in size classes by ny (powers of
- * two); for each class in turn the heights 32, 48, 64, 96, 128, 192, 256 are
- * timed with the other classes fixed and the fastest kept.  Members created
- * with their own tile_rows keep it.  The choice is kept in-process for the
+ * two); for all of them together, then for each class in turn, the heights in
+ * use, the default ones and 32, 48, 64, 96, 128, 192, 256 are timed with the
+ * other classes fixed and the fastest kept.  Members created with their own tile_rows keep it.  The choice is kept in-process for the
  * batch's composition (precision, geometry and every member's nx, ny in
  * order) and taken by later fvna_batch_create calls with the same
  * composition.  Results are bitwise independent of the heights.  Waits for
@@ -384,7 +384,9 @@ fvna_status fvna_batch_time_step_kernel(fvna_batch* b, int32_t reps, double* ms_
  * so the simulations are unchanged.  tile_rows (may be NULL) receives n
  * heights. */
 fvna_status fvna_batch_autotune(fvna_batch* b, int32_t* tile_rows);
-/* The n members' segment heights. */
+/* The n members' segment heights: their own, those fvna_batch_autotune chose, or
+ * the default, 96.  The default is an upper limit: a batch that can run in one
+ * round of wavefronts is cut into the shorter segments that suit it. */
 fvna_status fvna_batch_get_tile_rows(fvna_batch* b, int32_t* tile_rows);
 void fvna_batch_destroy(fvna_batch* b);
 

@@ -324,7 +324,7 @@ __global__ void k_batch_clocks(const SimDesc* __restrict__ descs, Clock* __restr
     for (int k = threadIdx.x; k < (int)(sizeof(Clock) / 8); k += blockDim.x) o[k] = src[k];
 }
 
-__global__ void k_clear_cfl(Clock* c)
+__device__ __forceinline__ void clear_cfl(Clock* c)
 {
     if (threadIdx.x >= 3) return;
     unsigned long long* sb;
@@ -333,6 +333,11 @@ __global__ void k_clear_cfl(Clock* c)
     *sb = 0ull;
     *fl = 0u;
 }
+
+__global__ void k_clear_cfl(Clock* c) { clear_cfl(c); }
+
+// The same for every simulation of a batch, one block each.
+__global__ void k_clear_cfl_batch(const SimDesc* __restrict__ descs) { clear_cfl(descs[blockIdx.x].clk); }
 
 __global__ void k_set_clock(Clock* c, Clock h)
 {
@@ -1581,35 +1586,57 @@ static SimDesc rejecting(SimDesc d)
     return d;
 }
 
-// Mean time of an attempt as the steps of a run make it, over a run of a
-// millisecond at least.  (Launches of the kernel alone, with no decision to
-// take, are dealt to the CUs otherwise where the blocks fill part of a round:
-// FP32 1024 x 768 in 8 / 16 rows 17.4 / 18.9 us alone, 21.9 / 19.5 in a run.)
-static fvna_status time_attempts(fvna_ctx* c, double* ms)
+// Mean time of an attempt as the steps of a run make it: in captured runs of
+// them, of about a millisecond each.  attempt(pos, stream) launches one of rejecting
+// simulations, clear(stream) what removes the speeds they leave (those of other
+// time steps).  The kernel launched alone is no guide where its blocks fill part
+// of a round: FP32 1024 x 768 in 8 / 16 rows takes 17.4 / 18.9 us with no
+// decision to take, 21.9 / 21.5 launched one by one, 21.7 / 19.5 in a graph.
+extern "C++" template <typename Attempt, typename Clear>
+static fvna_status time_attempts(hipStream_t stream, hipStream_t cap, double* ms, Attempt&& attempt, Clear&& clear)
 {
-    const SimDesc d = rejecting(c->d);
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
-    *ms = 0.25;
-    for (int warm = 1; warm >= 0; --warm) {
-        const int reps = warm ? 2 : std::max(4, std::min(24, (int)(1.0 / std::max(*ms, 1e-3))));
-        c->L.step(d, RecDesc{}, 1, 0, 1, c->stream);
-        HIP_TRY(hipEventRecord(e0, c->stream));
-        for (int k = 1; k <= reps; ++k) c->L.step(d, RecDesc{}, 1, k, 1, c->stream);
+    auto timed = [&](int n, auto&& launch) -> fvna_status {
+        HIP_TRY(hipEventRecord(e0, stream));
+        const fvna_status s = launch();
+        if (s) return s;
         HIP_TRY(hipGetLastError());
-        HIP_TRY(hipEventRecord(e1, c->stream));
-        // the speeds left behind are those of other time steps
-        hipLaunchKernelGGL(k_clear_cfl, dim3(1), dim3(64), 0, c->stream, c->clk);
+        HIP_TRY(hipEventRecord(e1, stream));
+        clear(stream);
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipEventSynchronize(e1));
         float t = 0.f;
         HIP_TRY(hipEventElapsedTime(&t, e0, e1));
-        *ms = (double)t / reps;
-    }
+        *ms = (double)t / n;
+        return FVNA_OK;
+    };
+    hipGraph_t g = nullptr;
+    hipGraphExec_t x = nullptr;
+    auto run = [&]() -> fvna_status {
+        fvna_status s = timed(1, [&] { attempt(0, stream); return FVNA_OK; });
+        if (s) return s;
+        const int n = std::max(4, std::min(GRAPH_CHUNK, (int)(1.0 / std::max(*ms, 1e-3))));
+        HIP_TRY(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
+        for (int k = 0; k < n; ++k) attempt(k, cap);
+        HIP_TRY(hipStreamEndCapture(cap, &g));
+        HIP_TRY(hipGraphInstantiate(&x, g, nullptr, nullptr, 0));
+        for (int launches : {1, 3}) {                  // the first one warms up
+            s = timed(n * launches, [&]() -> fvna_status {
+                for (int k = 0; k < launches; ++k) HIP_TRY(hipGraphLaunch(x, stream));
+                return FVNA_OK;
+            });
+            if (s) break;
+        }
+        return s;
+    };
+    const fvna_status s = run();
+    if (x) (void)hipGraphExecDestroy(x);
+    if (g) (void)hipGraphDestroy(g);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    return FVNA_OK;
+    return s;
 }
 
 fvna_status fvna_get_tile_rows(fvna_ctx* c, int32_t* tile_rows)
@@ -1650,7 +1677,10 @@ fvna_status fvna_autotune(fvna_ctx* c, int32_t* tile_rows)
     auto time_plan = [&](const std::pair<int, int>& pl, double* ms) -> fvna_status {
         set_segments(c->d, pl.first);
         c->d.block_rows = pl.second;
-        return time_attempts(c, ms);
+        const SimDesc d = rejecting(c->d);
+        return time_attempts(c->stream, c->cap, ms,
+                             [&](int pos, hipStream_t s) { c->L.step(d, RecDesc{}, 1, pos, 1, s); },
+                             [&](hipStream_t s) { hipLaunchKernelGGL(k_clear_cfl, dim3(1), dim3(64), 0, s, c->clk); });
     };
     double best = 1e30;
     std::pair<int, int> pick = plans[0];
@@ -1707,6 +1737,8 @@ struct fvna_batch {
     SimDesc* d_desc = nullptr;      // device copy of the descriptors
     TileRef* d_tiles = nullptr;
     Reply reply;                    // its tail: the members' clocks
+    int rows = 0;                   // default segment height (batch_rows)
+    std::vector<int> tuned;         // heights fvna_batch_autotune chose; 0: the default
     int ntiles = 0;
     int tile_cap = 0;               // TileRefs d_tiles can hold
     hipGraphExec_t exec = nullptr;
@@ -1716,7 +1748,7 @@ struct fvna_batch {
 namespace {
 
 // Batch autotune cache: (precision, geometry, the members' (nx, ny) in order)
-// -> the chosen segment height of each member.
+// -> the chosen segment height of each member, 0 for the default.
 typedef std::tuple<int, int, std::vector<std::pair<int, int>>> BatchKey;
 std::mutex g_btune_mu;
 std::map<BatchKey, std::vector<int>> g_btune;
@@ -1796,19 +1828,18 @@ fvna_status fvna_batch_create(int32_t n, const fvna_params* per_sim, void* const
     b->reply.tail = (size_t)n * sizeof(Clock);
     b->stream = (hipStream_t)hip_stream;
     b->L = pick_launcher(per_sim[0].precision, per_sim[0].geometry);
-    std::vector<int> tuned;
+    b->tuned.assign(n, 0);
     {
         std::lock_guard<std::mutex> g(g_btune_mu);
         auto it = g_btune.find(batch_key(per_sim, n));
-        if (it != g_btune.end()) tuned = it->second;
+        if (it != g_btune.end()) b->tuned = it->second;
     }
-    const int rows = batch_rows(per_sim, n, device_cu_count());
+    b->rows = batch_rows(per_sim, n, device_cu_count());
     for (int k = 0; k < n; ++k) {
         const fvna_params& p = per_sim[k];
         b->p.push_back(p);
         SimDesc d;
-        // or the heights fvna_batch_autotune chose for this composition
-        int tr = p.tile_rows ? p.tile_rows : (tuned.empty() ? rows : tuned[k]);
+        const int tr = p.tile_rows ? p.tile_rows : b->tuned[k] ? b->tuned[k] : b->rows;
         char* sc = (char*)bufs[3 * k + 2];
         fill_desc(d, &p, bufs[3 * k], bufs[3 * k + 1], (Clock*)(sc + OFF_CLOCK), tr, false);
         const fvna_status sr = fill_rinv(d, &p, sc, b->stream);
@@ -1955,7 +1986,8 @@ fvna_status fvna_batch_get_stats(fvna_batch* b, int32_t k, fvna_stats* st)
 
 // Upload the descriptors and tile table after a change of segment heights
 // (the captured graph holds the old tile count: dropped).
-static fvna_status batch_retile(fvna_batch* b)
+// reject: with the members' rejecting() forms.
+static fvna_status batch_retile(fvna_batch* b, bool reject = false)
 {
     if (b->exec || b->graph) {
         HIP_TRY(hipStreamSynchronize(b->stream));
@@ -1975,7 +2007,10 @@ static fvna_status batch_retile(fvna_batch* b)
         b->tile_cap = (int)tiles.size();
     }
     HIP_TRY(hipMemcpy(b->d_tiles, tiles.data(), sizeof(TileRef) * tiles.size(), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(b->d_desc, b->d.data(), sizeof(SimDesc) * b->n, hipMemcpyHostToDevice));
+    std::vector<SimDesc> d = b->d;
+    if (reject)
+        for (SimDesc& x : d) x = rejecting(x);
+    HIP_TRY(hipMemcpy(b->d_desc, d.data(), sizeof(SimDesc) * b->n, hipMemcpyHostToDevice));
     b->ntiles = (int)tiles.size();
     return FVNA_OK;
 }
@@ -1983,55 +2018,75 @@ static fvna_status batch_retile(fvna_batch* b)
 fvna_status fvna_batch_autotune(fvna_batch* b, int32_t* tile_rows)
 {
     if (!b) return fail(FVNA_E_INVALID, "batch is NULL");
-    // size classes by ny (powers of two); members with their own tile_rows keep it
+    // size classes by ny (powers of two), and first of all one of every member;
+    // members with their own tile_rows keep it
     std::map<int, std::vector<int>> cls;
     for (int k = 0; k < b->n; ++k)
         if (b->p[k].tile_rows == 0) {
             int c = 0;
             while ((2 << c) <= b->p[k].ny) ++c;
             cls[c].push_back(k);
+            cls[-1].push_back(k);
         }
-    const int cand[] = {32, 48, 64, 96, 128, 192, 256};
-    auto time_it = [&](double* ms) -> fvna_status {
-        fvna_status s = fvna_batch_time_step_kernel(b, 1, ms);      // warm-up
-        if (!s) s = fvna_batch_time_step_kernel(b, 5, ms);
-        return s;
-    };
-    // one pass of coordinate descent over the classes, smallest grids first
-    for (auto& kv : cls) {
-        const int cur = b->d[kv.second[0]].tile_rows;
-        double best = 1e30;
-        int best_tr = cur;
-        for (int tr : cand) {
-            bool useful = false;
-            for (int k : kv.second) useful = useful || tr < 2 * b->p[k].ny;
-            if (!useful) continue;
-            for (int k : kv.second) set_segments(b->d[k], tr, false);
-            fvna_status s = batch_retile(b);
-            double ms = 0.0;
-            if (!s) s = time_it(&ms);
+    if (cls.size() == 2) cls.erase(-1);
+    constexpr int IN_USE = -1;                     // else a height, or 0 for the default
+    auto tune = [&]() -> fvna_status {
+        // one pass of coordinate descent over the classes, smallest grids first
+        for (auto& kv : cls) {
+            const std::vector<int>& members = kv.second;
+            const std::vector<int> in_use = b->tuned;
+            auto set_class = [&](int h) {
+                for (int k : members) {
+                    b->tuned[k] = h == IN_USE ? in_use[k] : h;
+                    set_segments(b->d[k], b->tuned[k] ? b->tuned[k] : b->rows, false);
+                }
+            };
+            auto time_class = [&](int h, double* ms) -> fvna_status {
+                set_class(h);
+                const fvna_status s = batch_retile(b, true);
+                if (s) return s;
+                return time_attempts(b->stream, b->cap, ms, [&](int pos, hipStream_t st) {
+                    b->L.step_batch(b->d_desc, b->d_tiles, b->ntiles, 1, pos, 1, st);
+                }, [&](hipStream_t st) {
+                    hipLaunchKernelGGL(k_clear_cfl_batch, dim3(b->n), dim3(64), 0, st, b->d_desc);
+                });
+            };
+            int most = 0;
+            for (int k : members) most = std::max(most, b->p[k].ny);
+            double best = 1e30, ms = 0.0;
+            int pick = IN_USE;
+            fvna_status s = FVNA_OK;
+            for (int h : {IN_USE, 0, 32, 48, 64, 96, 128, 192, 256}) {
+                if (h > 0 && (h >= 2 * most || h == b->rows)) continue;
+                s = time_class(h, &ms);
+                if (s) break;
+                if (ms < best) { best = ms; pick = h; }
+            }
+            if (!s && pick != IN_USE) {
+                // the first one was timed on a device that may have been idle
+                s = time_class(IN_USE, &ms);
+                if (ms < 1.01 * best) pick = IN_USE;
+            }
+            set_class(s ? IN_USE : pick);
             if (s) return s;
-            if (ms < best) { best = ms; best_tr = tr; }
         }
-        for (int k : kv.second) set_segments(b->d[k], best_tr, false);
-    }
-    fvna_status s = batch_retile(b);
-    if (s) return s;
-    std::vector<int> chosen(b->n);
-    for (int k = 0; k < b->n; ++k) chosen[k] = b->d[k].tile_rows;
+        return FVNA_OK;
+    };
+    const fvna_status t = tune();
+    const fvna_status s = batch_retile(b);         // the members as they are again
+    if (t || s) return t ? t : s;
     {
         std::lock_guard<std::mutex> g(g_btune_mu);
-        g_btune[batch_key(b->p.data(), b->n)] = chosen;
+        g_btune[batch_key(b->p.data(), b->n)] = b->tuned;
     }
-    if (tile_rows)
-        for (int k = 0; k < b->n; ++k) tile_rows[k] = chosen[k];
-    return FVNA_OK;
+    return tile_rows ? fvna_batch_get_tile_rows(b, tile_rows) : FVNA_OK;
 }
 
 fvna_status fvna_batch_get_tile_rows(fvna_batch* b, int32_t* tile_rows)
 {
     if (!b || !tile_rows) return fail(FVNA_E_INVALID, "NULL argument");
-    for (int k = 0; k < b->n; ++k) tile_rows[k] = b->d[k].tile_rows;
+    for (int k = 0; k < b->n; ++k)
+        tile_rows[k] = b->p[k].tile_rows ? b->p[k].tile_rows : b->tuned[k] ? b->tuned[k] : BATCH_TILE_ROWS;
     return FVNA_OK;
 }
 

@@ -76,3 +76,38 @@ def test_autotuning_between_steps_changes_no_result():
         assert sa["rejected"] >= 1 and sa == sb
         for x, y in zip(a, b):
             assert np.array_equal(x, y)
+
+
+def test_autotuned_batch_is_no_slower():
+    """A batch small enough for one round of short segments, and a later one of
+    the same members; another batch's own heights are not handed on."""
+    from paper_1311_3004_amd import fvna
+    sizes = [(96, 96), (128, 128), (160, 160), (192, 192), (224, 224), (256, 256), (100, 250), (250, 100), (177, 211)]
+
+    def batch(tile_rows=0):
+        b = fvna.Batch([fvna.make_params(x, y, 1e-4, MED, precision="f64", tile_rows=tile_rows) for x, y in sizes])
+        for k, g in enumerate(sizes):
+            b.fvna_batch_set_state(k, *fields(*g))
+        return b
+
+    def step(b):
+        def run(n):
+            b.fvna_batch_step(n)
+            b.fvna_batch_sync()
+        return per_step(run)
+    a = batch()
+    before = step(a)
+    state = [a.fvna_batch_get_state(k) for k in range(len(sizes))]
+    stats = [a.fvna_batch_get_stats(k) for k in range(len(sizes))]
+    a.fvna_batch_autotune()
+    for k in range(len(sizes)):
+        assert a.fvna_batch_get_stats(k) == stats[k]
+        for x, y in zip(a.fvna_batch_get_state(k), state[k]):
+            assert np.array_equal(x, y)
+    b, own = batch(), batch(256)
+    assert own.fvna_batch_autotune() == [256] * len(sizes)
+    c = batch()
+    for s in (a, b, c):
+        assert step(s) < 1.25 * before
+    for s in (a, b, c, own):
+        s.fvna_batch_destroy()
