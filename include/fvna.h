@@ -339,13 +339,14 @@ fvna_status fvna_time_step_kernel(fvna_ctx* c, int32_t reps, double* ms_per_laun
 
 /* Pick tile_rows for this context by timing the next step's attempt with each
  * candidate, the plan in use and the library's default among them (state and
- * clock are unchanged); writes the chosen value to *tile_rows.  Contexts created later in the process
+ * clock are unchanged); writes the chosen value to *tile_rows (0: block tiles,
+ * as fvna_get_tile_rows).  Contexts created later in the process
  * for the same precision, geometry, nx and ny with tile_rows 0 take the choice.
  * Results are bitwise independent of it. */
 fvna_status fvna_autotune(fvna_ctx* c, int32_t* tile_rows);
 
-/* Rows per segment (or per block tile, on small grids) currently used by the
- * step kernel. */
+/* Rows per segment currently used by the step kernel, 0 where it runs in block
+ * tiles: the tile_rows with which fvna_create makes the same plan again. */
 fvna_status fvna_get_tile_rows(fvna_ctx* c, int32_t* tile_rows);
 
 /* Thread-local message of the last failing call (never NULL). */

@@ -1642,7 +1642,7 @@ static fvna_status time_attempts(hipStream_t stream, hipStream_t cap, double* ms
 fvna_status fvna_get_tile_rows(fvna_ctx* c, int32_t* tile_rows)
 {
     if (!c || !tile_rows) return fail(FVNA_E_INVALID, "NULL argument");
-    *tile_rows = c->d.block_rows > 0 ? c->d.block_rows : c->d.tile_rows;
+    *tile_rows = c->d.block_rows > 0 ? 0 : c->d.tile_rows;
     return FVNA_OK;
 }
 
@@ -1705,7 +1705,7 @@ fvna_status fvna_autotune(fvna_ctx* c, int32_t* tile_rows)
         std::lock_guard<std::mutex> g(g_tune_mu);
         g_tune[std::make_tuple(c->p.precision, c->p.geometry, c->p.nx, c->p.ny)] = best_block > 0 ? -best_block : best_tr;
     }
-    if (tile_rows) *tile_rows = best_block > 0 ? best_block : best_tr;
+    if (tile_rows) *tile_rows = best_block > 0 ? 0 : best_tr;
     return FVNA_OK;
 }
 

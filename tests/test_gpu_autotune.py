@@ -111,3 +111,24 @@ def test_autotuned_batch_is_no_slower():
         assert step(s) < 1.25 * before
     for s in (a, b, c, own):
         s.fvna_batch_destroy()
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32", "f32_f16store"])
+@pytest.mark.parametrize("nx,ny", [(96, 64), (101, 300), (512, 500), (1100, 1300)])
+@pytest.mark.parametrize("tune", [False, True])
+def test_tile_rows_handed_back_make_the_same_plan(nx, ny, precision, tune):
+    """What fvna_get_tile_rows and fvna_autotune answer is a value that
+    fvna_create takes, and the step of the context it makes takes as long."""
+    def step(s):
+        def run(n):
+            s.fvna_step(n)
+            s.fvna_sync()
+        return per_step(run)
+    a = context(nx, ny, precision)
+    rows = a.fvna_autotune() if tune else a.fvna_get_tile_rows()
+    assert rows == a.fvna_get_tile_rows()
+    b = context(nx, ny, precision, rows)
+    assert b.fvna_get_tile_rows() == rows
+    assert step(b) < 1.25 * step(a)
+    a.fvna_destroy()
+    b.fvna_destroy()
