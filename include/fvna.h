@@ -242,8 +242,8 @@ typedef struct {
 /* Advance nsteps accepted steps with the moving-domain rule above, updating
  * *st.  The checks and moves are decided on the device; waits for the stream
  * at the end of the call (and again for steps that rejected attempts left) and
- * returns the first device status that is not FVNA_OK (the steps of the
- * failing chunk are not all taken).  FVNA_E_INVALID for bad arguments or x
+ * every 1024 steps, and returns the first device status that is not FVNA_OK
+ * (the steps after the failing one are not taken).  FVNA_E_INVALID for bad arguments or x
  * sides that cannot move (as fvna_shift). */
 fvna_status fvna_step_window(fvna_ctx* c, const fvna_window* w, fvna_window_state* st, int64_t nsteps);
 

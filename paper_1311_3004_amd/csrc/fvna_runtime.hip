@@ -531,6 +531,7 @@ fvna_status fail(fvna_status s, const std::string& msg)
 constexpr size_t ALIGN = 256;
 constexpr size_t STAGE_CELLS = size_t(1) << 20;   // staging chunk for set/get state
 constexpr int GRAPH_CHUNK = 32;                   // attempts per captured graph
+constexpr int WINDOW_AHEAD = 1024;                // attempts fvna_step_window enqueues between looks at the clock
 // Segment height of batched simulations without their own when the batch runs
 // in several rounds of wavefronts: 64 uneven grids, us per step at 48 / 64 / 96
 // / 128 rows 806 / 793 / 782 / 812.  Smaller batches: batch_rows.
@@ -1318,28 +1319,36 @@ fvna_status fvna_step_window(fvna_ctx* c, const fvna_window* w, fvna_window_stat
     r.init.phase = st->phase;
     r.init.left = nsteps;
     r.init.seg = std::min<int64_t>(nsteps, w->check_every - st->phase);
-    // The whole call is enqueued segment by segment (the attempts up to a
-    // check, the check, the move); the host waits once, and again only for
-    // what rejected attempts (or steps owed from before) left over.  With the
-    // host deciding every check, 240 steps of a 480 x 800 FP64 packet with a
-    // check every 5 took 9.4 ms, 2.9 of them waiting.
-    int64_t left = nsteps, phase = st->phase, owed = r.init.seg;
-    for (int guard = 0; guard < 1000; ++guard) {
-        while (left > 0) {
-            const int64_t k = std::min<int64_t>(left, w->check_every - phase);
-            const bool check = guard > 0 || phase + k == w->check_every;
-            for (int64_t done = 0; done < k;) {
+    // The call is enqueued segment by segment (the attempts up to a check, the
+    // check, the move), WINDOW_AHEAD attempts at most before the host looks at
+    // the clock: an error found on the device or a move too large ends the call
+    // there.  Otherwise the host waits once, and again only for what rejected
+    // attempts (or steps owed from before) left over.  With the host deciding
+    // every check, 240 steps of a 480 x 800 FP64 packet with a check every 5
+    // took 9.4 ms, 2.9 of them waiting.
+    int64_t left = nsteps, phase = st->phase, owed = r.init.seg, accepted = -1;
+    int64_t pending = 0, seg = 0;      // attempts that complete the segment a look at the clock found running, its steps
+    for (int look = 0, idle = 0; idle < 1000; ++look) {
+        int64_t ahead = 0;
+        while ((left > 0 || pending > 0) && ahead < WINDOW_AHEAD) {
+            const int64_t steps = pending > 0 ? seg : std::min<int64_t>(left, w->check_every - phase);
+            const int64_t k = pending > 0 ? pending : steps;
+            pending = 0;
+            const bool check = look > 0 || phase + k == w->check_every;
+            int64_t done = 0;
+            while (done < k && ahead < WINDOW_AHEAD) {
                 const int n = (int)std::min<int64_t>(k - done, GRAPH_CHUNK);
                 done += n;
+                ahead += n;
                 r.may_move = check && done == k;
                 launch_attempts(c, n, owed, r, c->stream);
                 r.first = 0;
                 owed = 0;
             }
-            if (check) c->L.shift(c->d, c->stream);
+            if (r.may_move) c->L.shift(c->d, c->stream);
             HIP_TRY(hipGetLastError());
-            left -= k;
-            phase = (phase + k) % w->check_every;
+            left -= steps;
+            phase = (phase + steps) % w->check_every;
         }
         struct { Clock clk; char gap[WIN_OFFSET - sizeof(Clock)]; WinState win; } h;
         static_assert(sizeof(h) <= REPLY_HEAD && sizeof(h) % 8 == 0, "the clock area is read in words");
@@ -1350,8 +1359,13 @@ fvna_status fvna_step_window(fvna_ctx* c, const fvna_window* w, fvna_window_stat
         if (h.win.halted) return fail(FVNA_E_INVALID, "moving-domain jump too large");
         if (h.clk.status) return status_of(h.clk.status);
         if (h.win.left == 0 && h.win.phase < w->check_every) return FVNA_OK;
-        left = std::max<int64_t>(h.win.left, 1);
-        phase = std::min<int64_t>(h.win.phase, w->check_every - 1);
+        idle = h.clk.accepted > accepted ? 0 : idle + 1;
+        accepted = h.clk.accepted;
+        left = h.win.left;
+        phase = h.win.phase;
+        seg = h.win.seg;
+        // at least one attempt: a check that is due comes with it
+        pending = std::max<int64_t>(h.clk.target - h.clk.accepted, 1);
     }
     return fail(FVNA_E_STATE, "steps still owed after many top-up rounds");
 }
