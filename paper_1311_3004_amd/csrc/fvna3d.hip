@@ -787,6 +787,17 @@ int cu_count3()
     return n;
 }
 
+// Blocks of k3_sweep12 that a CU holds at once, as built.
+template <typename T> int resident12()
+{
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k3_sweep12<T>, 256, 0) != hipSuccess || n <= 0) {
+        (void)hipGetLastError();
+        n = sizeof(T) == 8 ? 2 : 5;
+    }
+    return n;
+}
+
 // Tiles of k3_sweep3s: the width bx, with by = threads / bx rows, and the
 // number of z segments of least cost, counted in planes pushed one after
 // another: rounds of one block per CU, times planes per segment + 6.
@@ -968,28 +979,30 @@ fvna_status fvna3_create(const fvna3_params* p, void* buf_a, void* buf_b, void* 
     // wavefronts let the dispatcher even out the load of the SIMDs, where
     // one round leaves some with a wavefront more than others (256^3, per
     // step: FP32 325 us with 43-row tiles, 333 with 64, 345 with 86, 371 with
-    // 128; 332 with 25).  A grid too small for that at 16 rows has all its tiles
-    // resident at once, and the CU with the most blocks (of four tiles) ends
-    // the sweep: m blocks on it take a row 1, 1.55, 2.15, ... = 0.35 + 0.6 m times
-    // as long as one (128^3 FP32: 0.93 us with one, 1.37, 1.88, 2.42, 2.93), and
-    // the height of least (rows + 4 warm-up rows) x that is taken, at least 4.
-    // us per step, by the total of tiles before / by blocks: 128^3 FP32 70 / 62
-    // (16 / 19 rows), FP64 103 / 90, 180 x 160 x 140 FP32 106 / 93 (32 / 24),
-    // 90 x 75 x 64 FP64 43 / 41 (10 / 5).
+    // 128; 332 with 25).  On a grid too small for that at 16 rows the CU with the
+    // most blocks (of four tiles) ends the sweep: m blocks on it take a row 1,
+    // 1.55, 2.15, ... = 0.35 + 0.6 m times as long as one (128^3 FP32: 0.93 us with
+    // one, 1.37, 1.88, 2.42, 2.93), blocks past what is resident (FP64 two per CU,
+    // FP32 five) take rounds, and the height of least (rows + 4 warm-up rows) x
+    // that is taken, at least 4.  us per step, by the total of tiles before / by
+    // blocks: 128^3 FP32 70 / 62 (16 / 19 rows), FP64 103 / 90, 180 x 160 x 140 FP32
+    // 106 / 93 (32 / 24), 90 x 75 x 64 FP64 43 / 41 (10 / 5); FP64 with three blocks
+    // taken as resident / two: 160^3 160 / 155 (27 / 40), 148 x 95 x 137 89 / 85
+    // (12 / 19), 96^3 59.5 / 57.3 (6 / 10).
     {
         const long long units = (long long)d.strips12 * p->nz + d.tailk12;
         const long long simds = 4ll * cus, want = 6 * simds;
         const long long nseg = std::max(1ll, (want + units - 1) / units);
         long long rows = (p->ny + nseg - 1) / nseg;
         if (rows < 16) {
-            const int resident = p->precision == FVNA_F64 ? 3 : 5;         // blocks of k3_sweep12 on a CU
+            const long long resident = p->precision == FVNA_F64 ? resident12<double>() : resident12<float>();
+            auto row_time = [](long long m) { return m == 0 ? 0.0 : m == 1 ? 1.0 : 0.35 + 0.6 * (double)m; };
             double best = 1e30;
             for (long long r = std::min(4, p->ny); r <= p->ny; ++r) {
-                const long long blocks = (units * ((p->ny + r - 1) / r) + 3) / 4, most = (blocks + cus - 1) / cus;
-                // past what is resident, blocks start as others end
-                const double m = most <= resident ? (double)most : (double)blocks / cus + 0.5;
-                const double cost = (double)(r + 2 * HALO12) * (most == 1 ? 1.0 : 0.35 + 0.6 * m);
-                if (cost < best) { best = cost; rows = r; }
+                const long long blocks = (units * ((p->ny + r - 1) / r) + 3) / 4, round = resident * cus;
+                const double cost = (double)(r + 2 * HALO12) * ((double)(blocks / round) * row_time(resident) +
+                                                                row_time((blocks % round + cus - 1) / cus));
+                if (cost <= best) { best = cost; rows = r; }       // of equals the tallest: fewer warm-up rows
             }
         }
         d.rows12 = (int)std::min(rows, (long long)p->ny);
