@@ -684,9 +684,16 @@ struct Plan { int rows; double us; };
 // measured, with T rows (T + 6 with the warm-up):
 //   FP64 n = 1: 5 + 0.95 (T + 6) us, n = 2: 5 + 1.53 (T + 6);
 //   FP32 n = 1: 4 + 0.70 (T + 6), n = 2: 4.5 + 0.93 (T + 6), n = 3: 12 + 1.20 (T + 6)
-// (within 8% over 720^2 .. 4096^2), and the least is taken: FP32 1000^2 n = 1
-// 21.8 us per step (n = 2: 28), 2000^2 n = 2 43.2 (n = 1: 66, n = 3: 50), 4096^2
-// n = 3 135 (n = 2: 151).  Never fewer than 8 rows.
+// where the round is full (within 8% over 720^2 .. 4096^2), and the least is
+// taken: FP32 1000^2 n = 2 18.7 us per step (9 rows; n = 1, 19 rows: 21.3), 2000^2
+// n = 2 39.0 (n = 1: 66, n = 3: 50), 4096^2 n = 3 135 (n = 2: 151).  Never fewer
+// than 8 rows.  On a grid too small for them the round is not full: the first
+// segments, as tall as the others there, end the step (EDGE_US), and with n = 2
+// blocks are dealt unevenly (FP32 1024 x 768, 8 rows: 21.9 us, 17.5 expected).
+// Added for segments of 8 rows, which have no shorter ones at the ends, at n = 1:
+// FP32 600^2 20.6 us per step (13.8 without it; 10 rows 15.5), FP64 23.7 (18.3; 20.0).
+constexpr double EDGE_US = 5.0;
+
 const double* row_cost(bool f64, int n)
 {
     static const double d[][2] = {{5.0, 0.95}, {5.0, 1.53}}, f[][2] = {{4.0, 0.70}, {4.5, 0.93}, {12.0, 1.20}};
@@ -716,7 +723,7 @@ Plan segment_plan(const fvna_params* p, int cu_count)
     for (int n = 1; n <= most; ++n) {
         const long long tr = rows_for((long long)std::max(cu_count, 1) * 4 * n);
         const double* c = row_cost(d, n);
-        const double us = c[0] + c[1] * (double)(tr + 2 * HALO);
+        const double us = c[0] + c[1] * (double)(tr + 2 * HALO) + (n == 1 && tr == 8 ? EDGE_US : 0.0);
         if (us < best.us) best = Plan{(int)tr, us};
     }
     return best;
@@ -770,9 +777,9 @@ Plan block_plan(const fvna_params* p, int cu_count)
 
 // Rows of a block tile, or 0 for segments: whichever plan expects the shorter
 // step.  The line comes out near half a million cells.  Measured us per step,
-// block tiles / segments: FP64 96^2 8.4 / 17.2, 360^2 12.5 / 20.1, 720^2 22.1 /
-// 21.6, 1300^2 46.4 / 39.1; FP32 360^2 10.6 / 15.5, 720^2 16.9 / 17.3, 1000^2
-// 23.1 / 21.8, 2000^2 60.4 / 43.2.
+// block tiles / segments: FP64 96^2 8.4 / 17.2, 360^2 12.5 / 20.1, 600^2 19.3 / 20.0,
+// 720^2 22.1 / 19.9, 1300^2 46.4 / 34.7; FP32 360^2 10.6 / 15.5, 600^2 14.4 / 15.5,
+// 720^2 16.9 / 15.4, 1000^2 23.1 / 18.7, 2000^2 60.4 / 39.0.
 static int block_rows_for(const fvna_params* p, int cu_count)
 {
     const Plan b = block_plan(p, cu_count);

@@ -132,3 +132,20 @@ def test_tile_rows_handed_back_make_the_same_plan(nx, ny, precision, tune):
     assert step(b) < 1.25 * step(a)
     a.fvna_destroy()
     b.fvna_destroy()
+
+
+@pytest.mark.parametrize("nx,ny", [(600, 600), (700, 560), (2000, 200)])
+@pytest.mark.parametrize("precision", ["f32", "f32_f16store"])
+def test_default_plan_near_the_line_between_the_kernels(nx, ny, precision):
+    """Where segments of 8 rows and block tiles were expected to take the same
+    time to the last bit, the segments were taken (1.4 times as long as those of
+    10 rows)."""
+    def step(s):
+        def run(n):
+            s.fvna_step(n)
+            s.fvna_sync()
+        return per_step(run)
+    a, b = context(nx, ny, precision), context(nx, ny, precision, 10)
+    assert step(a) < 1.15 * step(b)
+    a.fvna_destroy()
+    b.fvna_destroy()
