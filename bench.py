@@ -33,7 +33,7 @@ BYTES_PER_CELL = {"f64": 48, "f32": 24, "f32_f16store": 12, "f32_bf16store": 12}
 # Counter figures of the step kernels on this workload (4096 x 4096), from
 # rocprofv3 --pmc runs of this script: HBM bytes per launch from FETCH_SIZE,
 # then WRITE_SIZE, each scaled by what the same counter reads for a plain
-# device copy (fetch x1.988, write x1.000), and VALU lane-ops per
+# device copy (fetch x1.991, write x1.000), and VALU lane-ops per
 # cell-update from SQ_INSTS_VALU x 64 / cells, and SIMD issue cycles per
 # cell-update from SQ_ACTIVE_INST_VALU (quad-cycles, summed over waves) x 4 /
 # cells, which also counts the extra cycles of transcendental instructions
@@ -44,18 +44,18 @@ BYTES_PER_CELL = {"f64": 48, "f32": 24, "f32_f16store": 12, "f32_bf16store": 12}
 # after any change they report null until profiled again.
 PMC_SOURCES = ("csrc/fvna_device.hpp", "csrc/fvna_step.hpp", "csrc/fvna_runtime.hip", "build.py")
 _PROFILED = {
-    "csrc/fvna_device.hpp": "0fbf95b3c781188d7b080aab21983132e628c03b02a0d33e523ef15bedaabef9",
-    "csrc/fvna_step.hpp": "d49f4a8d20130d8b4d1139716c8ae2c507493b313527b901fe85feef9b14fa96",
-    "csrc/fvna_runtime.hip": "eeaeacb8a80b16f18e24fa419059f010c4127f83fc229213f6019f3aeb7ba962",
+    "csrc/fvna_device.hpp": "bbb5289e18f1f5e49a6b8f40e4810ebc86fed077279905c3781eeef388e20373",
+    "csrc/fvna_step.hpp": "255177b6bea8b2fe018279288ee202cb66421611a85c554742266d07b9f29758",
+    "csrc/fvna_runtime.hip": "46e4bc752473c22b4f21540df7c43f62358acdef00a2c13ea52357a0e90a2cea",
     "build.py": "0b96d334687a542c0a4c252f33e1b52c4a4d56c135c4ae89b01618e48ecc776c",
 }
 PMC = {
     # profiles/k_step_f64_gaussian4096.md
-    "k_step<double,double,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 4.2271e+08, "write_bytes": 4.0461e+08,
+    "k_step<double,double,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 4.2287e+08, "write_bytes": 4.0455e+08,
                                 "valu_lane_ops_per_cell": 375.6, "valu_issue_cycles_per_cell": 24.99,
                                 "sources": _PROFILED},
     # profiles/k_step_f32_gaussian4096.md
-    "k_step<float,float,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 2.1489e+08, "write_bytes": 2.0268e+08,
+    "k_step<float,float,0>": {"nx": 4096, "ny": 4096, "fetch_bytes": 2.1517e+08, "write_bytes": 2.0297e+08,
                               "valu_lane_ops_per_cell": 287.9, "valu_issue_cycles_per_cell": 18.95,
                               "sources": _PROFILED},
 }
@@ -177,11 +177,11 @@ def other_configs(fvna, inputs, steps):
 
 
 def three_d(n=256, steps=200, precision="f32"):
-    """The 3-D step (fused x1-x2 sweep, x3 sweep, source and a device-side
-    controller, replayed from a HIP graph) on an n^3 Gaussian pulse (sigma 8
+    """The 3-D step (fused x1-x2 sweep, x3 sweep with the source, decisions on
+    the device, replayed from a HIP graph) on an n^3 Gaussian pulse (sigma 8
     cells, 2 MPa, 0.5% noise, seed 5), extrapolating sides, in FP32 or FP64:
     whole steps per second (host clock around fvna3_step, which waits once at
-    its end) and the mean duration of the three kernels of one step (HIP
+    its end) and the mean duration of the two kernels of one step (HIP
     events) against 32 B (FP32) or 64 B (FP64) per cell-update (read and
     write of four fields)."""
     import time

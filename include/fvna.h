@@ -360,9 +360,10 @@ void fvna_destroy(fvna_ctx* c);
  * bufs holds 3 n device pointers: state_a, state_b, scratch of simulation k
  * at 3k, 3k+1, 3k+2, sized by fvna_workspace_size of per_sim[k].  All must use
  * the same precision and geometry.  Each step of fvna_batch_step is one
- * launch of the batched kernel over the tiles of every simulation followed by
- * one launch of the per-simulation controller; nsteps steps are replayed from
- * a captured HIP graph.  Results are bitwise those of n separate contexts. */
+ * launch of the batched kernel over the tiles of every simulation, which first
+ * takes each simulation's decision on the attempt before; one launch closes a
+ * run of attempts.  Runs of 32 are replayed from a captured HIP graph, the rest
+ * launched directly.  Results are bitwise those of n separate contexts. */
 fvna_status fvna_batch_create(int32_t n, const fvna_params* per_sim, void* const* bufs,
                               void* hip_stream, fvna_batch** out);
 fvna_status fvna_batch_set_state(fvna_batch* b, int32_t k, const double* rho_p,

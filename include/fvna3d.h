@@ -11,12 +11,12 @@
  * FVNA_BC_EXTRAP0, FVNA_BC_REFLECT (fvna.h).  Errors are fvna_status values,
  * with fvna3_last_error() describing the last failing call.
  *
- * On the device a step is three kernels and a controller: the x1 and x2
- * sweeps of z-plane tiles fused (lanes along x1, a register march along x2,
- * every interface solved once), the x3 sweep (a register march along x3),
- * the source, then the accept/reject decision and the next time step on one
- * device thread.  Attempts are replayed from a captured HIP graph; the host
- * waits once per fvna3_step call.
+ * On the device a step is two kernels: the x1 and x2 sweeps of z-plane tiles
+ * fused (lanes along x1, a register march along x2, every interface solved
+ * once), then the x3 sweep (a register march along x3) with the source.  The
+ * accept/reject decision on an attempt and the next time step are taken in the
+ * prologues of the attempt after it.  Attempts are replayed from a captured HIP
+ * graph; the host waits once per fvna3_step call.
  */
 #ifndef FVNA3D_H
 #define FVNA3D_H
@@ -67,8 +67,8 @@ fvna_status fvna3_step(fvna3_ctx* c, int64_t nsteps);
 fvna_status fvna3_get_state(fvna3_ctx* c, double* rho_p, double* m1, double* m2, double* m3);
 fvna_status fvna3_get_stats(fvna3_ctx* c, fvna_stats* st);
 
-/* Mean duration in ms of the three kernels of one attempt without the
- * controller (reps recomputations back to back of the attempt the next step
+/* Mean duration in ms of the two kernels of one attempt without a decision to
+ * take (reps recomputations back to back of the attempt the next step
  * makes; the state and the clock are unchanged). */
 fvna_status fvna3_time_step_kernels(fvna3_ctx* c, int32_t reps, double* ms);
 

@@ -1145,8 +1145,8 @@ fvna_status fvna3_time_step_kernels(fvna3_ctx* c, int32_t reps, double* ms)
 {
     if (!c || !ms || reps < 1) return fail3(FVNA_E_INVALID, "bad argument");
     // back-to-back recomputations of the attempt the next step would make
-    // (forced, no controller): the state and the clock are unchanged apart
-    // from the attempt's speed maximum, which the next controller run clears
+    // (forced, no decision): the state and the clock are unchanged apart
+    // from the attempt's speed maximum, which the next closing launch clears
     hipEvent_t e0, e1;
     HIP3(hipEventCreate(&e0));
     HIP3(hipEventCreate(&e1));

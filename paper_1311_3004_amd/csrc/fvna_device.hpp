@@ -711,8 +711,8 @@ __device__ __forceinline__ Cell<T> x1_sweep(const Cell<T>& q, T dt, T beta, T hr
 // The transcendental functions and the divisions are calls, and what they
 // need of the lane and the clock is formed beside them (opaque keeps the
 // compiler from forming it ahead of the row loop).  Inlined, FP64 tanh, sine
-// and exponential made up half of a step kernel's code (205 of 116 KB for FP64
-// with them out), their constants pushed registers of the row loop to scratch,
+// and exponential made up almost half of a step kernel's code (FP64 205 KB, 116
+// with them out of line), their constants pushed registers of the row loop to scratch,
 // and the profiles of a tile's ghost rows, which do not change from row to
 // row, were evaluated ahead of the loop by every wavefront whatever the side
 // kinds (2600 cycles of each SIMD per wavefront).
@@ -1613,6 +1613,8 @@ __device__ __forceinline__ void block_march(const SimDesc& d, int strip, int r0,
                 if (DATA && tab.per != 0) {
                     // slots 0 .. half - 1: this wavefront's rows of the batches
                     // from here on, the others: the rows whose source it takes
+                    // (filled again after half batches, 8 or 32; block_plan on
+                    // 256 CUs chooses tiles of at most 8)
                     if (tslot == tab.slots() / 2) tslot = 0;
                     if (tslot == 0) {
                         const int half = tab.slots() / 2, sl = tab.slot_of(lane);

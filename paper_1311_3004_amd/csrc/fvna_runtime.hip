@@ -3,9 +3,9 @@
 // Responsibilities: validate parameters, convert SI to the dimensionless
 // variables of the paper's renormalisation with the mesh spacing as length
 // unit (Sec. 3, eqs. renorm and phi-tdelta), bind caller-owned device
-// buffers, launch the fused step kernel and the device-side time-step
-// controller, replay them from a captured HIP graph, and surface the device
-// status word at synchronisation.
+// buffers, launch the fused step kernel, whose prologues decide the attempts,
+// in runs (replayed from a captured HIP graph where they are long), and surface
+// the device status word at synchronisation.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -265,20 +265,6 @@ __global__ void k_rinv_table(T* __restrict__ tab, int ny)
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= ny + 2 * RINV_PAD) return;
     tab[k] = (T)(1.0 / ((double)(k - RINV_PAD) + 0.5));
-}
-
-// Whole clock of one simulation written from its arguments (every field the
-// controller and the step kernel read starts defined, counters at zero).
-__global__ void k_clock_init(Clock* __restrict__ c, double t, double dt, int cur, long long target)
-{
-    if (threadIdx.x != 0) return;
-    Clock h;
-    __builtin_memset(&h, 0, sizeof(h));
-    h.t = t;
-    h.dt = dt;
-    h.cur = cur;
-    h.target = target;
-    *c = h;
 }
 
 // Host doubles (SI, staged on the device) -> stored dimensionless field.
@@ -758,7 +744,10 @@ int batch_rows(const fvna_params* p, int n, int cu_count)
 // (LDS and registers).  Measured per batch: 2.85 us FP64, 2.0 us FP32 for a
 // block alone on its CU, 1.55 times that for two together, and 4.5 us per
 // launch, which with the blocks in rounds of two per CU gives the time of
-// every T within about 10%.
+// every T within about 10%.  Analytic sides, of which neither plan knows, take
+// longer in both kernels (FP64 us expected / measured, and segments of 10 rows:
+// 1044 x 503 with Taylor sides 17.8 / 24.0, 28.7; 480 x 800 axisymmetric with the
+// focused source 17.8 / 22.5, 20.3).
 Plan block_plan(const fvna_params* p, int cu_count)
 {
     const long long strips = (p->nx + OUTW - 1) / OUTW, cus = std::max(cu_count, 1);

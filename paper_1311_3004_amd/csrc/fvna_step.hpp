@@ -9,7 +9,7 @@
 namespace fvna {
 
 // Waves per SIMD the register allocation must allow: three for FP32 compute
-// (168 VGPRs, no spills; with tiles that fill every slot in one round this
+// (134 to 139 VGPRs; with tiles that fill every slot in one round this
 // measured 9% faster than four waves at 128 VGPRs on a 4096^2 grid and level
 // on 8192^2), two for FP64.
 #ifndef FVNA_F32_WAVES_PER_SIMD
@@ -35,9 +35,8 @@ __device__ __forceinline__ int xcd_block(int b, int nblocks)
 // One attempted step over the whole grid.  force = 1 (timing): run even when
 // no step is owed.
 // pos = 0: the attempt runs with the clock as it stands and its CFL maximum
-// goes to the clock (a controller launch decides after it).  pos >= 1 (the
-// attempts of a run after its first): the attempt first takes the decision on
-// the attempt before it itself.  Every wavefront computes it (control_next)
+// goes to the clock.  pos >= 1 (the attempts of a run after its first): the
+// attempt first takes the decision on the attempt before it itself.  Every wavefront computes it (control_next)
 // from that attempt's clock state -- the clock for pos = 1, shadow copy
 // (pos - 1) mod 2 after -- and its CFL slot (pos - 1) mod 3, none of which
 // this launch writes; the grid's first wavefront stores the result as shadow
